@@ -30,6 +30,7 @@
 #include "kernels_dense.hpp"
 #include "orth_mfma.hpp"
 #include "residual.hpp"
+#include "small_solve.hpp"
 #include "toeplitz.hpp"
 
 #include "cf_nu14.inc"
@@ -266,9 +267,10 @@ struct expmv_plan_s {
   // CF table on the device
   DevBuf<double> tau_re, tau_im, c_re, c_im;
   Workspace ws;
-  int* host_flags = nullptr;    // pinned, 2 slots x 4 ints
+  int* host_flags = nullptr;    // pinned: 2 slots x 4 ints, or one SmallResult
   hipEvent_t ev[2]{};
   int ldh = 0;
+  int max_row = 0;              // nonzeros of the longest row of K (and K^T)
   int last_inner_iters = 0;       // iterations of the previous inner solve
   double relax_scale = 1.0;       // inner tolerance factor (opts.inner_relax)
   KernelTimer kt;                 // opts.profile > 0
@@ -941,6 +943,67 @@ void amg_vcycle(expmv_plan_s* pl, AmgDev& H, int p, const T* b, T* out, int k,
   DISPATCH_PP(PP, amg_level<T, P_>(pl, H, 0, p, b, out, k, ctl, part_rz));
 }
 
+// Whether the Jacobi inner solve of a plan runs in one workgroup per column
+// (small_solve.hpp): the operator's rows fit one workgroup's registers.  Time
+// per iteration of one inner solve, launch and wait included, there and in the
+// streaming kernels (three launches for CG, five for BiCGStab):
+//   CG, 5-point, p = 4:        n = 1,024  1.6 and 16.0 us,  n = 3,969  2.4 and 16.7
+//   BiCGStab, 7-point, p = 3:  n = 1,728  3.8 and 37 us,    n = 3,375  5.0 and 35
+// Kernel timing (opts.profile) is a matter of the streaming kernels.
+bool small_solve(const expmv_plan_s* pl) {
+  return !pl->amg && pl->n <= (pl->symmetric ? kSmallRowsCg : kSmallRowsBcg) &&
+         pl->max_row <= kSmallWidth && pl->opts.profile <= 0;
+}
+
+template <typename T>
+InnerResult run_small_solve(expmv_plan_s* pl, int transpose, const T* src, double sign, T* out,
+                            int p) {
+  Workspace& w = pl->ws;
+  hipStream_t s = pl->stream;
+  const int n = int(pl->n);
+  const double tol = inner_tol_of(pl);
+  const Csr<T> A = csr_of<T>(pl, transpose);
+  static_assert(sizeof(SmallResult) <= sizeof(CgState) && sizeof(SmallResult) <= sizeof(BcgState),
+                "the result takes the place of the solver's state");
+  SmallResult* res = pl->symmetric ? reinterpret_cast<SmallResult*>(w.cgst)
+                                   : reinterpret_cast<SmallResult*>(w.bcgst);
+  auto launch = [&](auto kernel, int nt, int rows, int nred, int nvec) {
+    const size_t lds = sizeof(double) * nred * (nt / 64) + sizeof(T) * size_t(nvec) * nt * rows;
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    hipLaunchKernelGGL(kernel, dim3(p), dim3(nt), lds, s, n, p, sign, A.rowptr, A.colind, A.val,
+                       A.dinv, src, out, tol * tol, pl->opts.inner_maxit, res);
+  };
+  // 512 threads (two wavefronts per SIMD, 256 registers each) for every n: the
+  // rows per thread grow with n
+#define SMALL_CASE(W_, RC_, RB_)                                                \
+  do {                                                                          \
+    if (pl->symmetric) launch(k_small_cg<T, W_, RC_, 512>, 512, RC_, 3, 3);     \
+    else launch(k_small_bcg<T, W_, RB_, 512>, 512, RB_, 5, 5);                  \
+  } while (0)
+#define SMALL_DISPATCH(W_)                      \
+  do {                                          \
+    if (n <= 512) SMALL_CASE(W_, 1, 1);         \
+    else if (n <= 1024) SMALL_CASE(W_, 2, 2);   \
+    else if (n <= 2048) SMALL_CASE(W_, 4, 4);   \
+    else SMALL_CASE(W_, 8, 7);                  \
+  } while (0)
+  if (pl->max_row <= 6) SMALL_DISPATCH(6);
+  else SMALL_DISPATCH(7);
+#undef SMALL_DISPATCH
+#undef SMALL_CASE
+  HIPCHK(hipMemcpyAsync(pl->host_flags, res, sizeof(SmallResult), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipEventRecord(pl->ev[0], s));
+  HIPCHK(hipEventSynchronize(pl->ev[0]));
+  const SmallResult* h = reinterpret_cast<const SmallResult*>(pl->host_flags);
+  InnerResult r{0, 0};
+  for (int c = 0; c < p; ++c) {
+    r.iters = std::max(r.iters, h->iters[c]);
+    r.hit_cap |= h->hit_cap[c];
+  }
+  return r;
+}
+
 // out = K^{-1} (sign * src) by batched Jacobi-PCG (K SPD); out is the iterate.
 template <typename T>
 InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p) {
@@ -1116,6 +1179,7 @@ InnerResult apply_inverse(expmv_plan_s* pl, int transpose, const T* V, T* Wout, 
     toeplitz_gsf<T>(pl, transpose, V, Wout, p, -1.0 / pl->t);
     return {0, 0};
   }
+  if (small_solve(pl)) return run_small_solve<T>(pl, transpose, V, -1.0, Wout, p);
   if (pl->symmetric) return inner_cg<T>(pl, V, -1.0, Wout, p);
   return inner_bicgstab<T>(pl, transpose, V, -1.0, Wout, p);
 }
@@ -2272,9 +2336,9 @@ void upload_cf(expmv_plan_s* pl) {
 
 void init_plan_common(expmv_plan_s* pl) {
   HIPCHK(hipGetDevice(&pl->device));
-  HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&pl->host_flags), sizeof(int) * 8,
+  HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&pl->host_flags), sizeof(SmallResult),
                        hipHostMallocDefault));
-  std::memset(pl->host_flags, 0, sizeof(int) * 8);
+  std::memset(pl->host_flags, 0, sizeof(SmallResult));
   HIPCHK(hipEventCreateWithFlags(&pl->ev[0], hipEventDisableTiming));
   HIPCHK(hipEventCreateWithFlags(&pl->ev[1], hipEventDisableTiming));
   if (pl->opts.profile > 0) {
@@ -2354,6 +2418,8 @@ expmv_status build_csr(expmv_plan_s* pl, const int32_t* rowptr_d, const int32_t*
     }
   }
   pl->symmetric = sym;
+  for (int64_t i = 0; i < n; ++i)
+    pl->max_row = std::max({pl->max_row, rp[i + 1] - rp[i], rpt[i + 1] - rpt[i]});
   std::vector<double> dinv(n);
   for (int64_t i = 0; i < n; ++i) dinv[i] = 1.0 / diag[i];
   pl->rowptr.alloc(n + 1);
