@@ -229,7 +229,7 @@ __device__ inline void row_dot_pair(const int32_t* __restrict__ aci, const T* __
 
 // One smoothing step or a residual on one level (see the mode bits).
 template <typename T, int PPL, int VW, int NT, bool SEG>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, SEG ? kCgWaves : 1)
 k_amg_step(int k, const KrylovCtl* ctl, int n, int p, int G, const int32_t* __restrict__ rowptr,
            const int32_t* __restrict__ colind, const T* __restrict__ val,
            const T* __restrict__ dinv, const T* __restrict__ b, const T* __restrict__ x,
@@ -301,7 +301,7 @@ k_amg_step(int k, const KrylovCtl* ctl, int n, int p, int G, const int32_t* __re
 
 // bc = R r (restriction to the next level; R = P^T in CSR)
 template <typename T, int PPL, int VW, int NT, bool SEG>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, SEG ? kCgWaves : 1)
 k_amg_restrict(int k, const KrylovCtl* ctl, int nc, int p, int G,
                const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
                const T* __restrict__ val, const T* __restrict__ r, T* __restrict__ bc) {
@@ -324,7 +324,7 @@ k_amg_restrict(int k, const KrylovCtl* ctl, int nc, int p, int G,
 
 // x = x_base + P xc with x_base = x, or s0 D^{-1} b (mode kAmgX0)
 template <typename T, int PPL, int VW, int NT, bool SEG>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, SEG ? kCgWaves : 1)
 k_amg_prolong(int k, const KrylovCtl* ctl, int n, int p, int G,
               const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
               const T* __restrict__ val, const T* __restrict__ xc,
@@ -475,7 +475,7 @@ __device__ __forceinline__ void affine_pair_rows(int k, const KrylovCtl* ctl, in
 }
 
 template <typename T, int PPL, int VW, int NT, bool SEG>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, SEG ? kCgWaves : 1)
 k_amg_affine_pair(int k, const KrylovCtl* ctl, int n, int p, int G,
                   const int32_t* __restrict__ arp, const int32_t* __restrict__ aci,
                   const T* __restrict__ av, const T* __restrict__ dinv, const T* __restrict__ b,

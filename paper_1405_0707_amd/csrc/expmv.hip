@@ -325,14 +325,21 @@ constexpr bool kWide4 = PP >= 4 && (sizeof(T) == 4 || PP >= 16);
 template <typename T, int PP>
 constexpr bool kWide8 = sizeof(T) == 4 && PP >= 16;
 
-// Lane width of the inner solvers' SpMMs (k_cg_a, k_bcg_s): two adjacent
-// columns per lane for even p (one otherwise), so that the eight gathers of a
-// pipelined row step (spmm_unroll) fit in the registers of a 1024-thread
-// workgroup with FP32 and FP64 blocks alike (four FP32 columns spilled).
-// Only the columns a lane owns change with the width: the rows of each
-// workgroup, and so the partial sums, do not.
+// Lane width of the inner solvers' SpMMs (k_cg_a, k_bcg_s, k_spmm): 16 bytes
+// of adjacent columns per lane (two FP64 columns for even p, four FP32 ones for
+// p a multiple of 4), so that the eight gathers of a row step (spmm_unroll) fit
+// 128 registers; else two FP32 columns, or one.  Only the columns a lane owns
+// change with the width: the rows of each workgroup, and so the partial sums,
+// do not.
 #define SPMM_DISPATCH(T, PP, p, ...)                                         \
   do {                                                                       \
+    if constexpr (PP >= 4 && sizeof(T) == 4) {                               \
+      if ((p) % 4 == 0) {                                                    \
+        constexpr int PPL_ = PP / 4, VW_ = 4;                                \
+        __VA_ARGS__;                                                         \
+        break;                                                               \
+      }                                                                      \
+    }                                                                        \
     if constexpr (PP >= 2) {                                                 \
       if ((p) % 2 == 0) {                                                    \
         constexpr int PPL_ = PP / 2, VW_ = 2;                                \
@@ -580,24 +587,31 @@ Csr<float> csr_of<float>(expmv_plan_s* pl, int transpose) {
             : Csr<float>{pl->rowptr.p, pl->colind.p, pl->val.p, pl->dinvf.p};
 }
 
-// Y = K X (K = -tA, or its transpose) for n x p blocks of type T.
 template <typename T>
 void toeplitz_apply(expmv_plan_s* pl, const T* X, int64_t ldx, T* Y, int64_t ldy, int p,
                     double scale, int accumulate, int transpose = 0, bool with_diag = true);
 template <typename T>
 void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, double scale);
 
+int cg_grid(int64_t n, int PP);
+
+// Whether the SpMMs stage the operator's entries through LDS (spmm_rows).
+int staged_rows(const expmv_plan_s* pl) { return pl->nnz <= 8 * pl->n ? 1 : 0; }
+
+// Y = scale K X (K = -tA, or its transpose) for n x p blocks of type T.
 template <typename T>
-void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p) {
+void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double scale = 1.0) {
   if (pl->kind == 1) {   // K = t T (or t T^T)
-    toeplitz_apply<T>(pl, X, p, Y, p, p, pl->t, 0, transpose);
+    toeplitz_apply<T>(pl, X, p, Y, p, p, scale * pl->t, 0, transpose);
     return;
   }
   Csr<T> A = csr_of<T>(pl, transpose);
   const int PP = pow2_lanes(p);
-  const int grid = grid_for(pl->n, PP, 4096);
-  DISPATCH_PP(PP, hipLaunchKernelGGL((k_spmm<T, P_>), dim3(grid), dim3(kThreads), 0, pl->stream,
-                                     int(pl->n), p, A.rowptr, A.colind, A.val, X, Y));
+  DISPATCH_PP(PP, SPMM_DISPATCH(T, P_, p,
+                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(cg_grid(pl->n, PP)),
+                                                   dim3(kCgThreads), 0, pl->stream, int(pl->n), p,
+                                                   A.rowptr, A.colind, A.val, staged_rows(pl), X, Y,
+                                                   scale)));
 }
 
 struct KtEv {
@@ -648,8 +662,8 @@ struct InnerResult {
 };
 
 int cg_grid(int64_t n, int PP) {
-  return int(std::max<int64_t>(
-      1, std::min<int64_t>(kCgGrid, (n * PP + kCgThreads - 1) / kCgThreads)));
+  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(kCgGrid, (n * PP + 1023) / 1024));
+  return int(g < 8 ? g : (g + 7) / 8 * 8);
 }
 
 double inner_tol_of(expmv_plan_s* pl) {
@@ -849,9 +863,10 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
     restrict_fused(reinterpret_cast<T*>(C.vb), xc, false);
     const KtEv e = kt_take(pl, c_prol, csr(n, L.nnz_a) + es * n + blk + csr(n, L.nnz_p) + cblk +
                                            blk);
-    hipExtLaunchKernelGGL((k_amg_affine_pair<T, PPL, VW, kCgThreads, true>), dim3(gfine),
-                          dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k, ctl, n, p, std::max(GA, GP),
-                          L.arp, L.aci, lv.a, dinv, b, L.Prp.p, L.Pci.p, lv.p, xc, L.alpha, L.beta,
+    const int G = std::max(GA, GP);
+    hipExtLaunchKernelGGL((k_amg_affine_pair<T, PPL, VW, kCgThreads, true>),
+                          dim3(cg_grid(n, 2 * PPL * G)), dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k,
+                          ctl, n, p, G, L.arp, L.aci, lv.a, dinv, b, L.Prp.p, L.Pci.p, lv.p, xc, L.alpha, L.beta,
                           x);
   } else {
     // pre-smoothing from zero: the first step's iterate s0 D^{-1} b stays implicit
@@ -1073,7 +1088,7 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
                                     hipExtLaunchKernelGGL((k_cg_a<T, PPL_, VW_>), dim3(grid),
                                                           dim3(kCgThreads), 0, s, ea.e0, ea.e1, 0,
                                                           k, int(n), p, A.rowptr, A.colind, A.val,
-                                                          pnew, q, w.ctl, w.part_sig)));
+                                                          staged_rows(pl), pnew, q, w.ctl, w.part_sig)));
       const KtEv eb = kt_take(pl, EXPMV_KT_CG_RESID, by_b);
       DISPATCH_CG(PP, p, hipExtLaunchKernelGGL((k_cg_b<T, PPL_, VW_>), dim3(grid),
                                                dim3(kCgThreads), 0, s, eb.e0, eb.e1, 0, k, int(n),
@@ -1091,12 +1106,12 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
 
 template <typename T, int PP, int NV>
 void bcg_spmm(hipStream_t s, KtEv e, int grid, int i, int n, int p, const int32_t* rowptr,
-              const int32_t* colind, const double* val, const T* dinv, const T* in, const T* a,
-              T* out, const KrylovCtl* ctl, double* part) {
+              const int32_t* colind, const double* val, int staged, const T* dinv, const T* in,
+              const T* a, T* out, const KrylovCtl* ctl, double* part) {
   SPMM_DISPATCH(T, PP, p,
                 hipExtLaunchKernelGGL((k_bcg_s<T, PPL_, VW_, NV>), dim3(grid), dim3(kCgThreads),
-                                      0, s, e.e0, e.e1, 0, i, n, p, rowptr, colind, val, dinv,
-                                      in, a, out, ctl, part));
+                                      0, s, e.e0, e.e1, 0, i, n, p, rowptr, colind, val, staged,
+                                      dinv, in, a, out, ctl, part));
 }
 
 // out = K^{-1} (sign * src) (or K^{-T}) by batched BiCGStab with right
@@ -1147,7 +1162,7 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
                                             p, r, pv, v, w.bcgst, w.ctl, w.part_rr, tol2, maxit));
         if (H) amg_vcycle<T>(pl, *H, p, pv, ph, i, w.ctl, nullptr);
         bcg_spmm<T, P_, 1>(s, kt_take(pl, EXPMV_KT_BCG_SPMM1, by_s), grid, i, int(n), p, A.rowptr,
-                           A.colind, A.val, dscale, H ? ph : pv, rh, v, w.ctl, w.part_sig);
+                           A.colind, A.val, staged_rows(pl), dscale, H ? ph : pv, rh, v, w.ctl, w.part_sig);
         const KtEv e2 = kt_take(pl, EXPMV_KT_BCG_U2, 3 * blk);
         UPD_DISPATCH(T, P_, p,
                       hipExtLaunchKernelGGL((k_bcg_u2<T, PPL_, VW_>), dim3(grid),
@@ -1155,7 +1170,7 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
                                             p, r, v, sv, w.bcgst, w.ctl, w.part_sig));
         if (H) amg_vcycle<T>(pl, *H, p, sv, sh, i, w.ctl, nullptr);
         bcg_spmm<T, P_, 2>(s, kt_take(pl, EXPMV_KT_BCG_SPMM2, by_s), grid, i, int(n), p, A.rowptr,
-                           A.colind, A.val, dscale, H ? sh : sv, sv, tv, w.ctl, w.part_sig);
+                           A.colind, A.val, staged_rows(pl), dscale, H ? sh : sv, sv, tv, w.ctl, w.part_sig);
         const KtEv e3 = kt_take(pl, EXPMV_KT_BCG_U3, by_u3);
         UPD_DISPATCH(T, P_, p,
                       hipExtLaunchKernelGGL((k_bcg_u3<T, PPL_, VW_>), dim3(grid),
@@ -2036,10 +2051,7 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
       inf.inner_iters += r.iters;
       inf.inner_maxit_hit += r.hit_cap;
     } else {
-      apply_K<T>(pl, transpose, Vj, Wk, p);
-      // M V = -K V
-      hipLaunchKernelGGL((k_convert<T, T>), dim3(512), dim3(kThreads), 0, s, int64_t(blk), Wk, Wk,
-                         -1.0);
+      apply_K<T>(pl, transpose, Vj, Wk, p, -1.0);   // M V = -K V
     }
     inf.block_apps += 1;
   };
@@ -3174,10 +3186,7 @@ expmv_status expmv_apply_operator(expmv_plan plan, int transpose, const double* 
   if (!plan || !X || !Y || p < 1 || p > kMaxP || p > plan->n) return EXPMV_EINVAL;
   return guarded([&]() -> expmv_status {
     bind_workspace(plan, int(p), 1, false, work, work_bytes);
-    apply_K<double>(plan, transpose, X, Y, int(p));
-    const int64_t cnt = plan->n * p;
-    hipLaunchKernelGGL((k_convert<double, double>), dim3(512), dim3(kThreads), 0, plan->stream, cnt,
-                       Y, Y, -1.0);
+    apply_K<double>(plan, transpose, X, Y, int(p), -1.0);
     HIPCHK(hipGetLastError());
     return EXPMV_OK;
   });

@@ -4,7 +4,7 @@
 // workgroups and a grid-stride loop over rows; a group of PP lanes (PP = p
 // rounded up to a power of two, PP | 64) owns one row, so every row's p
 // values are one contiguous, coalesced segment.  The inner-solver kernels
-// (1024-thread workgroups) give each lane VW = 2 adjacent columns when p is
+// (kCgThreads-thread workgroups) give each lane VW = 2 adjacent columns when p is
 // even, so PPL = PP / 2 lanes own a row and loads are 16 bytes wide; for odd
 // p, VW = 1 and PPL = PP.  Reductions are
 // deterministic: per-workgroup partial sums in a fixed tree order, then a
@@ -18,7 +18,14 @@
 namespace expmv {
 
 constexpr int kThreads = 256;
-constexpr int kCgThreads = 1024;   // workgroup size of the inner-solver kernels
+// Workgroup size of the inner-solver kernels and their wavefronts per SIMD (128
+// registers): their 512 workgroups are resident at once, two per CU, so that
+// each pays its opening reduction once and one computes while the other waits
+// at a barrier.  With 1024 threads (one per CU, two generations) the SpMM of
+// the 128^3 operator at p = 16 took 281 us against 243, the CG's direction
+// update at 64^3, p = 8, 25.6 against 21.0 us.
+constexpr int kCgThreads = 512;
+constexpr int kCgWaves = 4;
 constexpr int kNShift = 7;   // conjugate-pair poles of the degree-14 CF form
 constexpr int kMaxP = 32;    // widest supported block
 
@@ -111,52 +118,30 @@ __device__ inline void xcd_rows(int64_t n, int64_t& r0, int64_t& r1) {
   r1 = min<int64_t>(n, r0 + per);
 }
 
-// acc (+)= sum_e val[e] * x[colind[e] * ld + c] over one CSR row, in order,
-// eight nonzeros per step with every load of a step issued before the first
-// product (predicated, no serial tail): a stencil row costs one round trip
-// for its indices and one for its gathers.
-// The operator's values are FP64 for every working type T: in the mixed
-// form the FP32 inner solver thus works with the exact operator (rounding
-// its entries to FP32 would move the eigenvalues of a non-normal operator
-// by the eigenvector condition number times 6e-8).
-template <typename T>
-__device__ inline T csr_row_dot(const int32_t* __restrict__ colind, const double* __restrict__ val,
-                                const T* __restrict__ x, int e0, int e1, int ld, int c) {
-  constexpr int U = 8;
-  double acc = 0.0;
-  for (int e = e0; e < e1; e += U) {
-    int32_t j[U];
-    double v[U], w[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ok = e + u < e1;
-      j[u] = ok ? colind[e + u] : -1;
-      v[u] = ok ? val[e + u] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = j[u] >= 0 ? double(x[int64_t(j[u]) * ld + c]) : 0.0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc += v[u] * w[u];
-  }
-  return T(acc);
-}
-
-// ---------------------------------------------------------------------------
-// CSR SpMM  y = K x  (n x p blocks, PP lanes per row)
-
-template <typename T, int PP>
-__global__ void __launch_bounds__(kThreads)
-k_spmm(int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-       const double* __restrict__ val, const T* __restrict__ x, T* __restrict__ y) {
-  const int c = threadIdx.x % PP;
-  const int64_t rows_per_grid = int64_t(gridDim.x) * (kThreads / PP);
-  for (int64_t row = int64_t(blockIdx.x) * (kThreads / PP) + threadIdx.x / PP; row < n;
-       row += rows_per_grid) {
-    if (c < p) {
-      y[row * p + c] = csr_row_dot(colind, val, x, rowptr[row], rowptr[row + 1], p, c);
+// Rows of a streaming kernel whose workgroups take `per` rows at a time: the
+// workgroups of one XCD stride together through the eighth of the rows that
+// xcd_rows gives that XCD, so that they read one contiguous window of each
+// array at a time (fewer open DRAM pages than one stream per workgroup): the
+// BiCGStab updates at 128^3, p = 16 went from 235 / 182 / 467 to 216 / 147 /
+// 420 us (5.1 TB/s, as a 1 GiB copy), the CG's residual update at 1024^2,
+// p = 32 in FP32 from 88 to 74 us.
+struct StreamRows {
+  int64_t r, end, step;
+  __device__ StreamRows(int64_t n, int per, int lane_row) {
+    const int G = gridDim.x, b = blockIdx.x;
+    if (G % 8 == 0) {
+      const int64_t eighth = (n + G - 1) / G * (G / 8);
+      const int64_t s0 = min<int64_t>(n, int64_t(b % 8) * eighth);
+      r = s0 + int64_t(b / 8) * per + lane_row;
+      end = min<int64_t>(n, s0 + eighth);
+      step = int64_t(G / 8) * per;
+    } else {
+      r = int64_t(b) * per + lane_row;
+      end = n;
+      step = int64_t(G) * per;
     }
   }
-}
+};
 
 // ---------------------------------------------------------------------------
 // Batched Jacobi-preconditioned CG on K x = b (K SPD), column-wise, the p
@@ -308,40 +293,6 @@ __device__ inline void st_vw(T* __restrict__ dst, const T (&o)[VW]) {
   }
 }
 
-// csr_row_dot for the VW columns c0 .. c0 + VW - 1 (sums in FP64)
-template <int VW, typename T>
-__device__ inline void csr_row_dot_vw(const int32_t* __restrict__ colind,
-                                      const double* __restrict__ val, const T* __restrict__ x,
-                                      int e0, int e1, int ld, int c0, double (&acc)[VW]) {
-  constexpr int U = 16 / (VW > 2 ? VW : 2);   // VW = 4, 8: same registers as VW = 2
-#pragma unroll
-  for (int q = 0; q < VW; ++q) acc[q] = 0.0;
-  for (int e = e0; e < e1; e += U) {
-    int32_t j[U];
-    double v[U];
-    T w[U][VW];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ok = e + u < e1;
-      j[u] = ok ? colind[e + u] : -1;
-      v[u] = ok ? val[e + u] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (j[u] >= 0) {
-        ld_vw<VW>(x + int64_t(j[u]) * ld + c0, w[u]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < VW; ++q) w[u][q] = T(0);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int q = 0; q < VW; ++q) acc[q] += v[u] * double(w[u][q]);
-  }
-}
-
 // Entries a0 .. a0 + U - 1 of a CSR row ending at a1 (j = -1, v = 0 past it).
 template <int U>
 __device__ inline void csr_entries(const int32_t* __restrict__ colind,
@@ -362,8 +313,12 @@ __device__ inline void csr_entries(const int32_t* __restrict__ colind,
 // flight, the first U entries of the next row and the extents of the row
 // after it are already being loaded.  Entries past the first U of a row
 // (rows longer than U) follow without prefetch.  The sum runs over the row's
-// entries in order, as csr_row_dot_vw does; inactive lanes (masked columns)
-// issue no gathers and get zero sums.
+// entries in order, in FP64; inactive lanes (masked columns) issue no
+// gathers and get zero sums.
+// The operator's values are FP64 for every working type T: in the mixed
+// form the FP32 inner solver thus works with the exact operator (rounding
+// its entries to FP32 would move the eigenvalues of a non-normal operator
+// by the eigenvector condition number times 6e-8).
 template <int U, int VW, typename T, typename Body>
 __device__ inline void csr_rows_pipelined(const int32_t* __restrict__ rowptr,
                                           const int32_t* __restrict__ colind,
@@ -449,20 +404,166 @@ __device__ inline void csr_rows_pipelined(const int32_t* __restrict__ rowptr,
   }
 }
 
+// Barrier of a workgroup that orders its LDS accesses only: global loads
+// issued before it (the next chunk's entries) stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// csr_rows_pipelined for the rows seg0 .. seg1 - 1 of a whole workgroup (NT
+// threads, PPL lanes per row), with the operator's entries staged through
+// LDS: a tile of NT / PPL rows owns one contiguous run of entries, which the
+// workgroup loads coalesced, S entries per thread and chunk, one chunk ahead
+// of the rows that use them (sj, sv: 2 S NT entries).  A row's index and
+// value then cost an LDS read shared by its lanes instead of two loads per
+// lane, so that a wavefront issues one gather per nonzero and little else,
+// and the gather waits for LDS instead of memory.  Same sums in the same
+// order.  Every thread of the workgroup runs the same chunks.
+// Bound: memory; the 128^3 product at p = 16 (7 nonzeros per row) takes 243 us in
+// the BiCGStab (1.34 GB counted, 5.5 TB/s) against 290 us for
+// csr_rows_pipelined, and 202 us alone (569 us with one column per lane and no
+// staging); in FP32 at 1024^2, p = 32, 147 against 232 us.
+template <int S, int U, int PPL, int VW, int NT, typename T, typename Body>
+__device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
+                                       const int32_t* __restrict__ colind,
+                                       const double* __restrict__ val, const T* __restrict__ x,
+                                       const T* __restrict__ dinv, int ld, int c0, bool active,
+                                       int64_t seg0, int64_t seg1, int32_t* sj, double* sv,
+                                       Body&& body) {
+  constexpr int TR = NT / PPL, CH = NT * S;
+  if (seg0 >= seg1) return;
+  const int tid = threadIdx.x;
+  int64_t r0 = seg0, row = seg0 + tid / PPL;
+  int cb = rowptr[seg0], tb = rowptr[min<int64_t>(seg0 + TR, seg1)],
+      tn = rowptr[min<int64_t>(seg0 + 2 * TR, seg1)];
+  int32_t js[S];
+  double vs[S];
+  auto fetch = [&](int b, int e) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int i = b + tid + s * NT;
+      js[s] = i < e ? colind[i] : 0;
+      vs[s] = i < e ? val[i] : 0.0;
+    }
+  };
+  auto extents = [&](int64_t r, int& a, int& b) {
+    a = b = 0;
+    if (r < seg1) {
+      a = rowptr[r];
+      b = rowptr[r + 1];
+    }
+  };
+  fetch(cb, min(cb + CH, tb));
+  int e0, e1, ne0, ne1;
+  extents(row, e0, e1);
+  extents(row + TR, ne0, ne1);
+  double acc[VW];
+#pragma unroll
+  for (int q = 0; q < VW; ++q) acc[q] = 0.0;
+  for (int buf = 0;; buf ^= CH) {
+    const int ce = min(cb + CH, tb);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int i = tid + s * NT;
+      if (cb + i < ce) {
+        sj[buf + i] = js[s];
+        sv[buf + i] = vs[s];
+      }
+    }
+    const bool last = ce >= tb;
+    fetch(ce, min(ce + CH, last ? tn : tb));
+    lds_barrier();
+    const int lo = max(e0, cb) - cb + buf, hi = min(e1, ce) - cb + buf;
+    for (int e = lo; e < hi; e += U) {
+      T w[U][VW];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (active && e + u < hi) {
+          const int32_t j = sj[e + u];
+          ld_vw<VW>(x + int64_t(j) * ld + c0, w[u]);
+          if (dinv) {
+            const T dj = dinv[j];
+#pragma unroll
+            for (int q = 0; q < VW; ++q) w[u][q] = dj * w[u][q];
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < VW; ++q) w[u][q] = T(0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double v = e + u < hi ? sv[e + u] : 0.0;
+#pragma unroll
+        for (int q = 0; q < VW; ++q) acc[q] += v * double(w[u][q]);
+      }
+    }
+    cb = ce;
+    if (!last) continue;
+    if (row < seg1) body(row, acc);
+    r0 += TR;
+    if (r0 >= seg1) break;
+    row += TR;
+    tb = tn;
+    tn = rowptr[min<int64_t>(r0 + 2 * TR, seg1)];
+    e0 = ne0;
+    e1 = ne1;
+    extents(row + TR, ne0, ne1);
+#pragma unroll
+    for (int q = 0; q < VW; ++q) acc[q] = 0.0;
+  }
+}
+
 // Entries per pipelined row step of the inner solver's SpMM: 8 (a 7-point
 // stencil row in one step) for up to 16 bytes of columns per lane; wider
-// lanes take 4, as 8 would spill past the 128 VGPRs a wave of a 1024-thread
-// workgroup may hold.
+// lanes take 4, as 8 would spill past the 128 VGPRs of kCgWaves wavefronts per
+// SIMD.
 template <typename T, int VW>
 constexpr int spmm_unroll() {
   return (VW * sizeof(T) <= 16) ? 8 : 4;
+}
+
+// Entries per thread of a staged chunk (csr_rows_staged): a tile of
+// kCgThreads / PPL rows of up to 8 nonzeros is one chunk.  0 (one lane per row,
+// whose two chunks of entries would take 96 KB of LDS): not staged.
+template <int PPL>
+constexpr int spmm_stage() {
+  return PPL >= 8 ? 1 : (PPL >= 2 ? 8 / PPL : 0);
+}
+
+// The rows of this workgroup's segment (kCgThreads threads) of y = K x or K D^{-1} x:
+// body(row, sums).  staged: rows of at most 8 nonzeros on average (longer
+// rows would leave most lanes idle in each chunk).
+template <typename T, int PPL, int VW, typename Body>
+__device__ inline void spmm_rows(int staged, int64_t n, const int32_t* __restrict__ rowptr,
+                                 const int32_t* __restrict__ colind,
+                                 const double* __restrict__ val, const T* __restrict__ x,
+                                 const T* __restrict__ dinv, int ld, int c0, bool active,
+                                 Body&& body) {
+  int64_t seg0, seg1;
+  xcd_rows(n, seg0, seg1);
+  constexpr int S = spmm_stage<PPL>();
+  if constexpr (S > 0) {
+    __shared__ double sv[2 * S * kCgThreads];
+    __shared__ int32_t sj[2 * S * kCgThreads];
+    if (staged) {
+      csr_rows_staged<S, spmm_unroll<T, VW>(), PPL, VW, kCgThreads>(
+          rowptr, colind, val, x, dinv, ld, c0, active, seg0, seg1, sj, sv, body);
+      return;
+    }
+  }
+  csr_rows_pipelined<spmm_unroll<T, VW>(), VW>(rowptr, colind, val, x, dinv, ld, c0, active,
+                                               seg0 + threadIdx.x / PPL, kCgThreads / PPL, seg1,
+                                               body);
 }
 
 // The CG kernels take VW adjacent columns per lane (VW = 2 for even p) and
 // PPL = PP / VW lanes per row; per-column scalars and partials keep the layout
 // of PP columns.
 template <typename T, typename TS, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __restrict__ dinv,
           T* __restrict__ x, T* __restrict__ r, T* __restrict__ pold,
           KrylovCtl* ctl, double* __restrict__ part_rr, float* __restrict__ r32) {
@@ -472,9 +573,8 @@ k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __rest
   double rz[VW], bb[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) rz[q] = bb[q] = 0.0;
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  for (int64_t row = seg0 + threadIdx.x / PPL; row < seg1; row += kCgThreads / PPL) {
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t i = row * p + c0;
       TS sv[VW];
@@ -510,7 +610,7 @@ k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __rest
 // z: the preconditioned residual (TZ = float for an FP32 V-cycle), or NULL
 // for Jacobi (D^{-1} r formed here)
 template <typename T, typename TZ, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
        const TZ* __restrict__ z, const T* __restrict__ pold, T* __restrict__ pnew,
        T* __restrict__ x, CgState* st, KrylovCtl* ctl, const double* __restrict__ part_rr,
@@ -524,10 +624,9 @@ k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
   // the operands of this thread's first row are loaded before the scalar
   // reduction, so their latency overlaps it (they are final at kernel start)
   const int c0 = VW * (threadIdx.x % PPL);
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  const int64_t row0 = seg0 + threadIdx.x / PPL;
-  const bool pre = row0 < seg1 && c0 < p;
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const int64_t row0 = rows.r;
+  const bool pre = row0 < rows.end && c0 < p;
   T po0[VW], xv0[VW], zr0[VW];
   if (pre) {
     const int64_t i = row0 * p + c0;
@@ -606,7 +705,7 @@ k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
     aprev[q] = T(s_aprev[(c0 + q) % PP]);
   }
   const bool any = s_any != 0;
-  for (int64_t row = row0; row < seg1; row += kCgThreads / PPL) {
+  for (int64_t row = row0; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t i = row * p + c0;
       const bool first = row == row0;
@@ -654,9 +753,9 @@ k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
 }
 
 template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-       const double* __restrict__ val, const T* __restrict__ pk, T* __restrict__ q,
+       const double* __restrict__ val, int staged, const T* __restrict__ pk, T* __restrict__ q,
        const KrylovCtl* ctl, double* __restrict__ part_sig) {
   constexpr int PP = PPL * VW;
   if (finished_by(ctl, k)) return;
@@ -665,12 +764,10 @@ k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* _
   double sig[VW];
 #pragma unroll
   for (int u = 0; u < VW; ++u) sig[u] = 0.0;
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
   const bool active = c0 < p;
-  csr_rows_pipelined<spmm_unroll<T, VW>(), VW>(
-      rowptr, colind, val, pk, static_cast<const T*>(nullptr), p, c0, active,
-      seg0 + threadIdx.x / PPL, kCgThreads / PPL, seg1, [&](int64_t row, const double(&acc)[VW]) {
+  spmm_rows<T, PPL, VW>(
+      staged, n, rowptr, colind, val, pk, static_cast<const T*>(nullptr), p, c0, active,
+      [&](int64_t row, const double(&acc)[VW]) {
         if (!active) return;
         const int64_t i = row * p + c0;
         T qv[VW], pv[VW];
@@ -684,8 +781,27 @@ k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* _
   write_col_partial_vw<PPL, VW>(sig, red, part_sig, PP, 0);
 }
 
+// y = scale K x, in the launch shape of the inner solvers' products
 template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+k_spmm(int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
+       const double* __restrict__ val, int staged, const T* __restrict__ x, T* __restrict__ y,
+       double scale) {
+  const int c0 = VW * (threadIdx.x % PPL);
+  const bool active = c0 < p;
+  spmm_rows<T, PPL, VW>(
+      staged, n, rowptr, colind, val, x, static_cast<const T*>(nullptr), p, c0, active,
+      [&](int64_t row, const double(&acc)[VW]) {
+        if (!active) return;
+        T o[VW];
+#pragma unroll
+        for (int u = 0; u < VW; ++u) o[u] = T(scale * acc[u]);
+        st_vw<VW>(y + row * p + c0, o);
+      });
+}
+
+template <typename T, int PPL, int VW>
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const T* __restrict__ q,
        CgState* st, const KrylovCtl* ctl, const double* __restrict__ part_sig,
        double* __restrict__ part_rr, int jacobi, float* __restrict__ r32) {
@@ -696,10 +812,9 @@ k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const
   __shared__ double s_alpha[PP];
   // the first row's r and q are loaded before the scalar reduction
   const int c0 = VW * (threadIdx.x % PPL);
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  const int64_t row0 = seg0 + threadIdx.x / PPL;
-  const bool pre = row0 < seg1 && c0 < p;
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const int64_t row0 = rows.r;
+  const bool pre = row0 < rows.end && c0 < p;
   T rv0[VW], qv0[VW];
   if (pre) {
     ld_vw<VW>(r + row0 * p + c0, rv0);
@@ -723,7 +838,7 @@ k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const
   double rz[VW], rr[VW];
 #pragma unroll
   for (int u = 0; u < VW; ++u) rz[u] = rr[u] = 0.0;
-  for (int64_t row = row0; row < seg1; row += kCgThreads / PPL) {
+  for (int64_t row = row0; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t i = row * p + c0;
       T rv[VW], qv[VW];
@@ -784,15 +899,14 @@ struct BcgState {
 };
 
 template <typename T, typename TS, int PP>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_bcg_init(int n, int p, double sign, const TS* __restrict__ src, T* __restrict__ x,
            T* __restrict__ r, T* __restrict__ rhat, KrylovCtl* ctl, double* __restrict__ part_rr) {
   __shared__ double red[kCgThreads];
   const int c = threadIdx.x % PP;
   double bb = 0.0;
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  for (int64_t row = seg0 + threadIdx.x / PP; row < seg1; row += kCgThreads / PP) {
+  const StreamRows rows(n, kCgThreads / PP, threadIdx.x / PP);
+  for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c < p) {
       const int64_t i = row * p + c;
       const T b = T(sign * double(src[i]));
@@ -815,7 +929,7 @@ k_bcg_init(int n, int p, double sign, const TS* __restrict__ src, T* __restrict_
 // The three BiCGStab updates take VW adjacent columns per lane (PPL = PP / VW
 // lanes per row; VW = 2 for even p: 16-byte FP64 accesses) like the SpMM.
 template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_bcg_u1(int i, int n, int p, const T* __restrict__ r, T* __restrict__ pv, const T* __restrict__ v,
          BcgState* st, KrylovCtl* ctl, const double* __restrict__ part_rr, double tol2, int maxit) {
   constexpr int PP = PPL * VW;
@@ -893,9 +1007,8 @@ k_bcg_u1(int i, int n, int p, const T* __restrict__ r, T* __restrict__ pv, const
     beta[q] = T(s_beta[(c0 + q) % PP]);
     om[q] = T(s_om[(c0 + q) % PP]);
   }
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  for (int64_t row = seg0 + threadIdx.x / PPL; row < seg1; row += kCgThreads / PPL) {
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
       T rv[VW];
@@ -917,10 +1030,10 @@ k_bcg_u1(int i, int n, int p, const T* __restrict__ r, T* __restrict__ pv, const
 // out = K D^{-1} in (out = K in when dinv is NULL: the input is already
 // preconditioned), partials (a, out) [NV = 1] or (out, a), (out, out) [NV = 2]
 template <typename T, int PPL, int VW, int NV>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-        const double* __restrict__ val, const T* __restrict__ dinv, const T* __restrict__ in,
-        const T* __restrict__ a, T* __restrict__ out, const KrylovCtl* ctl,
+        const double* __restrict__ val, int staged, const T* __restrict__ dinv,
+        const T* __restrict__ in, const T* __restrict__ a, T* __restrict__ out, const KrylovCtl* ctl,
         double* __restrict__ part) {
   constexpr int PP = PPL * VW;
   if (finished_by(ctl, i)) return;
@@ -929,12 +1042,10 @@ k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* 
   double d0[VW], d1[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) d0[q] = d1[q] = 0.0;
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
   const bool active = c0 < p;
-  csr_rows_pipelined<spmm_unroll<T, VW>(), VW>(
-      rowptr, colind, val, in, dinv, p, c0, active, seg0 + threadIdx.x / PPL, kCgThreads / PPL,
-      seg1, [&](int64_t row, const double(&accd)[VW]) {
+  spmm_rows<T, PPL, VW>(
+      staged, n, rowptr, colind, val, in, dinv, p, c0, active,
+      [&](int64_t row, const double(&accd)[VW]) {
         if (!active) return;
         const int64_t idx = row * p + c0;
         T acc[VW], av[VW];
@@ -954,7 +1065,7 @@ k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* 
 }
 
 template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, T* __restrict__ sv,
          BcgState* st, const KrylovCtl* ctl, const double* __restrict__ part) {
   constexpr int PP = PPL * VW;
@@ -976,9 +1087,8 @@ k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, 
   T a[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) a[q] = T(s_a[(c0 + q) % PP]);
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  for (int64_t row = seg0 + threadIdx.x / PPL; row < seg1; row += kCgThreads / PPL) {
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
       T rv[VW], vv[VW];
@@ -992,7 +1102,7 @@ k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, 
 }
 
 template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads)
+__global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ pv,
          const T* __restrict__ sv, const T* __restrict__ tv, const T* __restrict__ rhat,
          const T* __restrict__ ph, const T* __restrict__ sh, T* __restrict__ x,
@@ -1027,9 +1137,8 @@ k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ 
   double rr_hat[VW], rr[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) rr_hat[q] = rr[q] = 0.0;
-  int64_t seg0, seg1;
-  xcd_rows(n, seg0, seg1);
-  for (int64_t row = seg0 + threadIdx.x / PPL; row < seg1; row += kCgThreads / PPL) {
+  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
       T sval[VW], xv[VW], tw[VW], rh[VW], u[VW], w[VW];
