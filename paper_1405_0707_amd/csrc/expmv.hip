@@ -962,8 +962,8 @@ void amg_vcycle(expmv_plan_s* pl, AmgDev& H, int p, const T* b, T* out, int k,
 // (small_solve.hpp): the operator's rows fit one workgroup's registers.  Time
 // per iteration of one inner solve, launch and wait included, there and in the
 // streaming kernels (three launches for CG, five for BiCGStab):
-//   CG, 5-point, p = 4:        n = 1,024  1.6 and 16.0 us,  n = 3,969  2.4 and 16.7
-//   BiCGStab, 7-point, p = 3:  n = 1,728  3.8 and 37 us,    n = 3,375  5.0 and 35
+//   CG, 5-point, p = 4:        n = 1,024  1.2 and 15.0 us,  n = 3,969  2.3 and 15.5
+//   BiCGStab, 7-point, p = 3:  n = 1,728  3.2 and 37 us,    n = 3,375  4.9 and 35
 // Kernel timing (opts.profile) is a matter of the streaming kernels.
 bool small_solve(const expmv_plan_s* pl) {
   return !pl->amg && pl->n <= (pl->symmetric ? kSmallRowsCg : kSmallRowsBcg) &&
@@ -989,21 +989,25 @@ InnerResult run_small_solve(expmv_plan_s* pl, int transpose, const T* src, doubl
     hipLaunchKernelGGL(kernel, dim3(p), dim3(nt), lds, s, n, p, sign, A.rowptr, A.colind, A.val,
                        A.dinv, src, out, tol * tol, pl->opts.inner_maxit, res);
   };
-  // 512 threads (two wavefronts per SIMD, 256 registers each) for every n: the
-  // rows per thread grow with n
-#define SMALL_CASE(W_, RC_, RB_)                                                \
+  // few wavefronts with several rows per thread: an iteration waits on its
+  // reductions and barriers more than on its arithmetic.  CG at n = 1,024 took
+  // 1.29 us with 256 threads, 1.43 with 512 and 2.60 with 1,024; BiCGStab 2.83,
+  // 3.03 and 4.87 us at n = 1,000, 3.86, 3.73 and 5.48 at n = 1,728
+#define SMALL_CASE(W_, NT_, RC_, RB_)                                           \
   do {                                                                          \
-    if (pl->symmetric) launch(k_small_cg<T, W_, RC_, 512>, 512, RC_, 3, 3);     \
-    else launch(k_small_bcg<T, W_, RB_, 512>, 512, RB_, 5, 5);                  \
+    if (pl->symmetric)                                                          \
+      launch(k_small_cg<T, W_, RC_, NT_>, NT_, RC_, 3, RC_ > 4 ? 3 : 1);        \
+    else                                                                        \
+      launch(k_small_bcg<T, W_, RB_, NT_>, NT_, RB_, 5, RB_ > 4 ? 5 : 1);       \
   } while (0)
 #define SMALL_DISPATCH(W_)                      \
   do {                                          \
-    if (n <= 512) SMALL_CASE(W_, 1, 1);         \
-    else if (n <= 1024) SMALL_CASE(W_, 2, 2);   \
-    else if (n <= 2048) SMALL_CASE(W_, 4, 4);   \
-    else SMALL_CASE(W_, 8, 7);                  \
+    if (n <= 512) SMALL_CASE(W_, 256, 2, 2);        \
+    else if (n <= 1024) SMALL_CASE(W_, 256, 4, 4);  \
+    else if (n <= 2048) SMALL_CASE(W_, 512, 4, 4);  \
+    else SMALL_CASE(W_, 512, 8, 7);                 \
   } while (0)
-  if (pl->max_row <= 6) SMALL_DISPATCH(6);
+  if (pl->max_row <= 5) SMALL_DISPATCH(5);
   else SMALL_DISPATCH(7);
 #undef SMALL_DISPATCH
 #undef SMALL_CASE

@@ -5,8 +5,8 @@
 // The streaming kernels of kernels.hpp cost three (CG) or five (BiCGStab)
 // launches per iteration, 3 to 5 us each plus the gap before it, whatever the
 // size: at n = 1,024, p = 4 a CG iteration took 16 us for 0.16 MB of operands,
-// and takes 1.6 us here (the whole e^{tA}B 32 -> 4.6 ms; the 7-point upwind
-// operator at n = 1,728, p = 3: 37 -> 3.8 us, 60 -> 12 ms).
+// and takes 1.2 us here (the whole e^{tA}B 32 -> 4.5 ms; the 7-point upwind
+// operator at n = 1,728, p = 3: 37 -> 3.2 us, 60 -> 11 ms).
 // Here the operator's rows (values and 16-bit column indices) stay in
 // registers for the whole solve, the vectors in registers and LDS, and an
 // iteration costs three (five) workgroup barriers and one LDS gather per
@@ -68,10 +68,15 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double* red) {
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    double s = red[k * NW];
+    double s[NW];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) s += red[k * NW + w];
-    v[k] = s;
+    for (int w = 0; w < NW; ++w) s[w] = red[k * NW + w];
+#pragma unroll
+    for (int h = NW / 2; h >= 1; h /= 2) {
+#pragma unroll
+      for (int w = 0; w < h; ++w) s[w] += s[w + h];
+    }
+    v[k] = s[0];
   }
 }
 
@@ -117,6 +122,29 @@ struct SmallRows {
   }
 };
 
+// A vector's own entries (rows tid + r NT) of a thread: registers, or LDS
+// where registers are short (R > 4: the operator's rows take 150 and more).
+// In LDS at n = 1,024 they cost as many LDS cycles as the gathers.
+template <typename T, int R, int NT, bool Lds>
+struct OwnRows {
+  T v[R];
+  __device__ __forceinline__ T get(int r) const { return v[r]; }
+  __device__ __forceinline__ void set(int r, T x) { v[r] = x; }
+};
+template <typename T, int R, int NT>
+struct OwnRows<T, R, NT, true> {
+  T* v;
+  __device__ __forceinline__ T get(int r) const { return v[threadIdx.x + r * NT]; }
+  __device__ __forceinline__ void set(int r, T x) { v[threadIdx.x + r * NT] = x; }
+};
+template <typename T, int R, int NT, bool Lds>
+__device__ __forceinline__ void own_place(OwnRows<T, R, NT, Lds>& o, T*& lds) {
+  if constexpr (Lds) {
+    o.v = lds;
+    lds += NT * R;
+  }
+}
+
 // x = K^{-1} (sign * src), column blockIdx.x, by Jacobi-CG: the recurrences,
 // the stopping test (|r| <= tol |b| on the recurrence residual) and the cap of
 // k_cg_c / k_cg_a / k_cg_b.
@@ -130,8 +158,10 @@ k_small_cg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
   extern __shared__ char small_lds[];
   double* red = reinterpret_cast<double*>(small_lds);   // 2 NW, NW
   T* sp = reinterpret_cast<T*>(red + 3 * NW);           // the direction
-  T* sd = sp + NT * R;                                  // D^{-1}
-  T* sx = sd + NT * R;                                  // the iterate
+  T* more = sp + NT * R;
+  OwnRows<T, R, NT, (R > 4)> dv, xv;                    // D^{-1}, the iterate
+  own_place(dv, more);
+  own_place(xv, more);
   const int c = blockIdx.x, tid = threadIdx.x;
   SmallRows<W, R, NT> A;
   A.load(n, rowptr, colind, val);
@@ -140,8 +170,8 @@ k_small_cg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
   for (int r = 0; r < R; ++r) {
     const int row = tid + r * NT;
     rv[r] = row < n ? T(sign * double(src[int64_t(row) * p + c])) : T(0);
-    sx[row] = T(0);
-    sd[row] = row < n ? dinv[row] : T(0);
+    xv.set(r, T(0));
+    dv.set(r, row < n ? dinv[row] : T(0));
     sp[row] = T(0);
   }
   double bn = 0.0, rho_prev = 0.0;
@@ -151,7 +181,7 @@ k_small_cg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const double rd = double(rv[r]);
-      s[0] += rd * double(sd[tid + r * NT]) * rd;
+      s[0] += rd * double(dv.get(r)) * rd;
       s[1] += rd * rd;
     }
     block_sums<2, NW>(s, red);
@@ -168,7 +198,7 @@ k_small_cg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = tid + r * NT;
-      sp[row] = sd[row] * rv[r] + beta * sp[row];
+      sp[row] = dv.get(r) * rv[r] + beta * sp[row];
     }
     __syncthreads();
     T q[R];
@@ -182,14 +212,14 @@ k_small_cg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
     const T alpha = T(sig[0] != 0.0 ? rho / sig[0] : 0.0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      sx[tid + r * NT] += alpha * sp[tid + r * NT];
+      xv.set(r, xv.get(r) + alpha * sp[tid + r * NT]);
       rv[r] = rv[r] - alpha * q[r];
     }
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int row = tid + r * NT;
-    if (row < n) x[int64_t(row) * p + c] = sx[row];
+    if (row < n) x[int64_t(row) * p + c] = xv.get(r);
   }
   if (tid == 0) {
     res->iters[c] = it;
@@ -208,10 +238,12 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
   extern __shared__ char small_lds[];
   double* red = reinterpret_cast<double*>(small_lds);   // 2 NW, NW, 2 NW
   T* sy = reinterpret_cast<T*>(red + 5 * NW);           // D^{-1} p, then D^{-1} s
-  T* sd = sy + NT * R;                                  // D^{-1}
-  T* sh = sd + NT * R;                                  // r^ = b
-  T* sx = sh + NT * R;                                  // the iterate
-  T* sp = sx + NT * R;                                  // the direction
+  T* more = sy + NT * R;
+  OwnRows<T, R, NT, (R > 4)> dv, hv, xv, pv;            // D^{-1}, r^ = b, iterate, direction
+  own_place(dv, more);
+  own_place(hv, more);
+  own_place(xv, more);
+  own_place(pv, more);
   const int c = blockIdx.x, tid = threadIdx.x;
   SmallRows<W, R, NT> A;
   A.load(n, rowptr, colind, val);
@@ -221,9 +253,10 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
     const int row = tid + r * NT;
     rv[r] = row < n ? T(sign * double(src[int64_t(row) * p + c])) : T(0);
     vv[r] = T(0);
-    sd[row] = row < n ? dinv[row] : T(0);
-    sh[row] = rv[r];
-    sx[row] = sp[row] = T(0);
+    dv.set(r, row < n ? dinv[row] : T(0));
+    hv.set(r, rv[r]);
+    xv.set(r, T(0));
+    pv.set(r, T(0));
   }
   double bn = 0.0, rho_prev = 1.0, a_prev = 1.0, om_prev = 1.0;
   int it = 0, hit = 0;
@@ -232,7 +265,7 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const double rd = double(rv[r]);
-      s[0] += double(sh[tid + r * NT]) * rd;
+      s[0] += double(hv.get(r)) * rd;
       s[1] += rd * rd;
     }
     block_sums<2, NW>(s, red);
@@ -249,16 +282,16 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = tid + r * NT;
-      const T pn = i == 0 ? rv[r] : rv[r] + beta * (sp[row] - om1 * vv[r]);
-      sp[row] = pn;
-      sy[row] = sd[row] * pn;
+      const T pn = i == 0 ? rv[r] : rv[r] + beta * (pv.get(r) - om1 * vv[r]);
+      pv.set(r, pn);
+      sy[row] = dv.get(r) * pn;
     }
     __syncthreads();
     double d[1] = {0.0};
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       vv[r] = T(A.dot(r, sy));
-      d[0] += double(sh[tid + r * NT]) * double(vv[r]);
+      d[0] += double(hv.get(r)) * double(vv[r]);
     }
     block_sums<1, NW>(d, red + 2 * NW);
     const double alpha = d[0] != 0.0 ? rho / d[0] : 0.0;
@@ -268,8 +301,8 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
     for (int r = 0; r < R; ++r) {
       const int row = tid + r * NT;
       rv[r] = rv[r] - a * vv[r];
-      sx[row] += a * sy[row];
-      sy[row] = sd[row] * rv[r];
+      xv.set(r, xv.get(r) + a * sy[row]);
+      sy[row] = dv.get(r) * rv[r];
     }
     __syncthreads();
     T t[R];
@@ -286,7 +319,7 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = tid + r * NT;
-      sx[row] += om * sy[row];
+      xv.set(r, xv.get(r) + om * sy[row]);
       rv[r] = rv[r] - om * t[r];
     }
     a_prev = alpha;
@@ -295,7 +328,7 @@ k_small_bcg(int n, int p, double sign, const int32_t* __restrict__ rowptr,
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int row = tid + r * NT;
-    if (row < n) x[int64_t(row) * p + c] = sx[row];
+    if (row < n) x[int64_t(row) * p + c] = xv.get(r);
   }
   if (tid == 0) {
     res->iters[c] = it;
