@@ -30,6 +30,7 @@
 #include "kernels_dense.hpp"
 #include "orth_mfma.hpp"
 #include "residual.hpp"
+#include "small_fft.hpp"
 #include "small_solve.hpp"
 #include "toeplitz.hpp"
 
@@ -1262,6 +1263,32 @@ void fft(expmv_plan_s* pl, const cplx* in, cplx* out, cplx* tmp, int q, double s
 }
 
 // the call's FFT work arrays must hold q complex columns
+// The passes of a length-L transform in one workgroup (small_fft.hpp); passes
+// = 0 when L is longer than `most` or has a prime factor above 5.
+SmallRadices small_radices(int64_t L, int most) {
+  SmallRadices rad{int(L), 0, {}};
+  if (L > most || L < 2) return rad;
+  int64_t rest = L;
+  for (int R : {8, 4, 2, 5, 3})
+    while (rest % R == 0) {
+      rad.r[rad.passes++] = static_cast<unsigned char>(R);
+      rest /= R;
+    }
+  if (rest != 1) rad.passes = 0;
+  return rad;
+}
+
+// Launch a kernel of small_fft.hpp: one workgroup per complex column, `cols`
+// columns of LDS beside the table.
+template <typename K, typename... Args>
+void launch_small_fft(expmv_plan_s* pl, K kernel, const SmallRadices& rad, int q, int cols,
+                      Args... args) {
+  const size_t lds = sizeof(cplx) * size_t(rad.len) * (1 + cols);
+  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  hipLaunchKernelGGL(kernel, dim3(q), dim3(kSmallFftThreads), lds, pl->stream, rad, args...);
+}
+
 void check_fft_buffers(expmv_plan_s* pl, int q) {
   if (q > pl->ws.fq) throw StatusError{EXPMV_EINVAL};
 }
@@ -1274,8 +1301,13 @@ void toeplitz_apply(expmv_plan_s* pl, const T* X, int64_t ldx, T* Y, int64_t ldy
   const cplx* sym = (transpose && !pl->tsym) ? pl->chatT.p : pl->chat.p;
   const double* dg = with_diag ? pl->tdiag.p : nullptr;
   const int q = (p + 1) / 2;
-  check_fft_buffers(pl, q);
   const int64_t L = pl->L, n = pl->n;
+  if (const SmallRadices rad = small_radices(L, kSmallFftProduct); rad.passes && !accumulate) {
+    launch_small_fft(pl, k_small_toeplitz<T>, rad, q, 1, int(n), p, X, ldx, Y, ldy, sym,
+                     transpose ? dg : nullptr, transpose ? nullptr : dg, scale / double(L));
+    return;
+  }
+  check_fft_buffers(pl, q);
   cplx *A = pl->ws.fb[0], *Bf = pl->ws.fb[1], *C = pl->ws.fb[2];
   hipStream_t s = pl->stream;
   hipLaunchKernelGGL((k_pack<T>), dim3(stream_grid(L * q)), dim3(kThreads), 0, s, n, p, ldx, q, L,
@@ -1308,19 +1340,27 @@ void toeplitz_gsf_n(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, do
   const bool tr = transpose && !pl->tsym;
   const double* di = pl->tdinv.p;
   const int q = (p + 1) / 2;
-  check_fft_buffers(pl, q);
   const int64_t n = pl->n;
-  const std::vector<int>& rad = pl->radices_n;
-  cplx *A = pl->ws.fb[0], *Bf = pl->ws.fb[1], *C = pl->ws.fb[2], *D = pl->ws.fb[3];
-  hipStream_t s = pl->stream;
-  const int g = stream_grid(n * q);
-  const double inv = 1.0 / double(n);
   // the first factor pair: spectra applied reversed (transposed factors)
   const cplx* f1 = tr ? pl->ncx.p : pl->nsj.p;
   const cplx* f2 = tr ? pl->ncz.p : pl->nsz.p;
   // the second pair
   const cplx* g1 = tr ? pl->nsj.p : pl->ncx.p;
   const cplx* g2 = tr ? pl->nsz.p : pl->ncz.p;
+  // lengths that fit one workgroup's LDS: 48 us per call at n = 1,000, p = 2,
+  // against 154 for the 32 launches below (n = 3,000, p = 16: 91 and 163)
+  if (const SmallRadices sr = small_radices(n, kSmallFftInverse); sr.passes) {
+    launch_small_fft(pl, k_small_gsf_n<T>, sr, q, 2, p, V, W, f1, f2, g1, g2,
+                     transpose ? nullptr : di, transpose ? di : nullptr, tr ? 0.0 : -1.0,
+                     tr ? -1.0 : 0.0, scale / (2.0 * pl->x0));
+    return;
+  }
+  check_fft_buffers(pl, q);
+  const std::vector<int>& rad = pl->radices_n;
+  cplx *A = pl->ws.fb[0], *Bf = pl->ws.fb[1], *C = pl->ws.fb[2], *D = pl->ws.fb[3];
+  hipStream_t s = pl->stream;
+  const int g = stream_grid(n * q);
+  const double inv = 1.0 / double(n);
   // A = V (rows scaled by 1/d in the forward product), twisted by D^{-1}
   // for the skew-circulant S(.)^T that acts first in T^{-1}
   hipLaunchKernelGGL((k_pack_twist<T>), dim3(g), dim3(kThreads), 0, s, n, p, int64_t(p), q, V,
@@ -1369,8 +1409,14 @@ void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, doub
   const cplx* b1 = tr ? gjy : gx;
   const cplx* b2 = tr ? gzjx : gzy;
   const int q = (p + 1) / 2;
-  check_fft_buffers(pl, q);
   const int64_t L = pl->L, n = pl->n;
+  // (66 us per call at n = 1,001, p = 2, against 110)
+  if (const SmallRadices rad = small_radices(L, kSmallFftInverse); rad.passes) {
+    launch_small_fft(pl, k_small_gsf<T>, rad, q, 2, int(n), p, V, W, a1, a2, b1, b2,
+                     transpose ? nullptr : di, transpose ? di : nullptr, scale / pl->x0);
+    return;
+  }
+  check_fft_buffers(pl, q);
   cplx *A = pl->ws.fb[0], *Bf = pl->ws.fb[1], *C = pl->ws.fb[2], *D = pl->ws.fb[3];
   hipStream_t s = pl->stream;
   const int g = stream_grid(L * q);
@@ -1542,8 +1588,10 @@ void shift_residuals(expmv_plan_s* pl, int transpose, const double* B, int p, co
                                        tau_im, R, part1));
   } else {
     // K X_j by the FFT product into R, then R = B + K X + tau X in place
-    for (int j = 0; j < kNShift; ++j)
-      toeplitz_apply<double>(pl, Xq + 2 * p * j, ldx, R + 2 * p * j, W, 2 * p, pl->t, 0, transpose);
+    // (one workgroup per column when L is short: all shifts in one launch)
+    const int step = small_radices(pl->L, kSmallFftProduct).passes ? W : 2 * p;
+    for (int j = 0; j < W; j += step)
+      toeplitz_apply<double>(pl, Xq + j, ldx, R + j, W, step, pl->t, 0, transpose);
     DISPATCH_PP(PP, hipLaunchKernelGGL((k_shift_residual<P_>), dim3(g1), dim3(kThreads), 0, s, n,
                                        p, nullptr, nullptr, nullptr, R, B, Xq, ldx, tau_re, tau_im,
                                        R, part1));
