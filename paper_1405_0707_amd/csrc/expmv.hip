@@ -31,6 +31,7 @@
 #include "orth_mfma.hpp"
 #include "residual.hpp"
 #include "small_fft.hpp"
+#include "small_orth.hpp"
 #include "small_solve.hpp"
 #include "toeplitz.hpp"
 
@@ -1616,6 +1617,19 @@ void shift_residuals(expmv_plan_s* pl, int transpose, const double* B, int p, co
   }
 }
 
+// Whether a block step of orthonormalize runs in one workgroup
+// (small_orth.hpp): up to four columns, a block in LDS, and a basis that one CU
+// reads (four times) and reduces (p^2 sums per panel) in less than the 53-60 us
+// of the 14 streaming launches.  A step takes 36 us there at n = 1,024, p = 4
+// (6 panels on average), 34 at n = 1,000, p = 2 (22 panels); at n = 4,096, p = 1
+// and 30 panels it lost (77 against 69 us with the product), and at n = 1,024,
+// p = 8 (509 against 433).
+bool small_orth(const expmv_plan_s* pl, int p, int npan) {
+  const int64_t blk = pl->n * p;
+  return p <= kSmallOrthCols && blk <= kSmallOrthBlock && npan * blk <= 81920 &&
+         npan * blk * p <= 184320 && pl->opts.profile <= 0;
+}
+
 // Orthonormalise W (n x p) against panels 0..npan-1 of Vb (two block
 // Gram-Schmidt passes), then CholQR2; the result goes to Vout.
 //   H != nullptr: H(0:npan*p, col0:col0+p) += coefficients of both passes,
@@ -1627,6 +1641,25 @@ void orthonormalize(expmv_plan_s* pl, int p, const T* Vb, int npan, T* W, T* Vou
                     int ldh, int col0, double* Rhat) {
   Workspace& w = pl->ws;
   hipStream_t s = pl->stream;
+  // shift of the fallback (shifted Cholesky QR): 11 (n p + p (p + 1)) u
+  // times trace(G), u = 2^-53 (the Gram matrices are FP64)
+  const double shift_rel = 11.0 * (double(pl->n) * p + double(p) * (p + 1)) * 0x1p-53;
+  if (small_orth(pl, p, npan)) {
+    const size_t lds = sizeof(double) * size_t(npan) * p * p + sizeof(T) * size_t(pl->n) * p;
+    auto launch = [&](auto kernel) {
+      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallOrthThreads), lds, s, int(pl->n), npan, Vb, W,
+                         Vout, H, ldh, col0, Rhat, shift_rel, w.flags);
+    };
+    switch (p) {
+      case 1: launch(k_orth_small<T, 1>); break;
+      case 2: launch(k_orth_small<T, 2>); break;
+      case 3: launch(k_orth_small<T, 3>); break;
+      default: launch(k_orth_small<T, 4>); break;
+    }
+    return;
+  }
   const int Oc = npan * p * p;
   T* Wt = reinterpret_cast<T*>(w.Wt);
   if (npan > 0) {
@@ -1642,9 +1675,6 @@ void orthonormalize(expmv_plan_s* pl, int p, const T* Vb, int npan, T* W, T* Vou
     int nwg = orth_pass<T>(pl, kUpdGram, p, static_cast<const T*>(nullptr), 0, W, Wt, nullptr);
     reduce_partials(pl, nwg, p * p, w.gram, nullptr, 0, 0, p, 0);
   }
-  // shift of the fallback (shifted Cholesky QR): 11 (n p + p (p + 1)) u
-  // times trace(G), u = 2^-53 (the Gram matrices are FP64)
-  const double shift_rel = 11.0 * (double(pl->n) * p + double(p) * (p + 1)) * 0x1p-53;
   hipLaunchKernelGGL(k_cholqr_factor, dim3(1), dim3(64), 0, s, p, w.gram, w.R1, w.Rinv,
                      npan > 0 ? w.w0 : nullptr, 1, nullptr, nullptr, 0, 0, 0, shift_rel,
                      w.flags);

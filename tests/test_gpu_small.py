@@ -79,3 +79,26 @@ def test_small_inverse_cap(skew):
     pl = Plan.csr(A.indptr, A.indices, A.data, 1.0, device=DEV, inner_maxit=3)
     with pytest.raises(Exception, match="status 7"):
         pl.apply_inverse(torch.ones(400, 4, dtype=torch.float64))
+
+
+# blocks of 1 to 4 columns at the edges of the one-workgroup block step (6,144
+# values of W, 81,920 of the basis), and p = 5 and larger blocks past them
+@pytest.mark.parametrize("nx,ny,p,m", [(9, 1, 1, 6), (64, 2, 1, 30), (64, 64, 1, 22), (95, 32, 2, 14),
+                                       (96, 32, 2, 12), (64, 32, 3, 13), (83, 37, 2, 12),
+                                       (48, 32, 4, 9), (48, 33, 4, 9), (30, 30, 5, 8)])
+@pytest.mark.parametrize("skew", [0.0, 0.5])
+def test_small_block_steps(nx, ny, p, m, skew):
+    """e^{tA}B with the one-workgroup kernels against the streaming ones (which
+    opts.profile selects).  Both stop at an error bound of 1e-12 relative to
+    ||Z||; rounding is about 1e-15 ||B||, and ||Z|| > 1e-3 ||B|| on these grids:
+    1e-10."""
+    print(f"[gpu-test] small block steps {nx}x{ny} p={p} skew={skew}", flush=True)
+    A = grid2d(nx, ny, skew)
+    B = np.random.default_rng(p).standard_normal((nx * ny, p))
+    Z = []
+    for profile in (0, 1000000):
+        pl = Plan.csr(A.indptr, A.indices, A.data, 2.0, device=DEV, m=m, profile=profile,
+                      inner_precond="jacobi")
+        out, info = pl.execute(torch.from_numpy(B), tol=1e-12)
+        Z.append(out.cpu().numpy())
+    assert np.linalg.norm(Z[0] - Z[1]) < 1e-10 * np.linalg.norm(Z[1])
