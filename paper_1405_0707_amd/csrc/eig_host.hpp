@@ -18,11 +18,13 @@ bool sym_eig(int n, const double* A, double* w, double* Q);
 // an eigenvalue is not finite.
 bool general_eig(int n, const double* A, double* wr, double* wi, double* Vr, double* Vi);
 
-// Upper Hessenberg form H = Q^T A Q of a general A (both n x n row-major),
-// handed from the first half of general_eig to the second.
+// Upper Hessenberg form H = Q^T A Q of a general A (n x n row-major), handed
+// from the first half of general_eig to the second.  Q = P_0 P_1 ... P_{n-3},
+// P_k = I - beta[k] v v^T with v in row k of refl, columns k + 1 .. k + len[k].
 struct HessForm {
   int n = 0;
-  std::vector<double> H, Q;
+  std::vector<double> H, refl, beta;
+  std::vector<int> len;
 };
 
 // The two halves of general_eig: eigenvalues (exact conjugate pairs), then

@@ -1755,27 +1755,35 @@ double host_now_ms() {
 // Returns the number of independent columns kept (dependent ones dropped).
 int host_orthonormalize_columns(int d, int k, std::vector<double>& P) {
   int kept = 0;
-  std::vector<double> out(size_t(d) * k, 0.0);
+  std::vector<double> cols(size_t(d) * k);   // column by column
+  for (int i = 0; i < d; ++i)
+    for (int c = 0; c < k; ++c) cols[size_t(c) * d + i] = P[size_t(i) * k + c];
+  auto dot = [d](const double* x, const double* y) {
+    double s[4] = {};
+    int i = 0;
+    for (; i + 4 <= d; i += 4)
+      for (int u = 0; u < 4; ++u) s[u] += x[i + u] * y[i + u];
+    for (; i < d; ++i) s[0] += x[i] * y[i];
+    return (s[0] + s[1]) + (s[2] + s[3]);
+  };
   for (int c = 0; c < k; ++c) {
-    std::vector<double> v(d);
-    for (int i = 0; i < d; ++i) v[i] = P[size_t(i) * k + c];
-    double n0 = 0.0;
-    for (double x : v) n0 += x * x;
-    n0 = std::sqrt(n0);
+    double* v = &cols[size_t(c) * d];
+    const double n0 = std::sqrt(dot(v, v));
     for (int pass = 0; pass < 2; ++pass)
       for (int q = 0; q < kept; ++q) {
-        double h = 0.0;
-        for (int i = 0; i < d; ++i) h += out[size_t(i) * k + q] * v[i];
-        for (int i = 0; i < d; ++i) v[i] -= h * out[size_t(i) * k + q];
+        const double* u = &cols[size_t(q) * d];
+        const double h = dot(u, v);
+        for (int i = 0; i < d; ++i) v[i] -= h * u[i];
       }
-    double nv = 0.0;
-    for (double x : v) nv += x * x;
-    nv = std::sqrt(nv);
+    const double nv = std::sqrt(dot(v, v));
     if (!(nv > 1e-10 * n0)) continue;
-    for (int i = 0; i < d; ++i) out[size_t(i) * k + kept] = v[i] / nv;
+    double* o = &cols[size_t(kept) * d];
+    for (int i = 0; i < d; ++i) o[i] = v[i] / nv;
     ++kept;
   }
-  P = out;
+  std::fill(P.begin(), P.end(), 0.0);
+  for (int i = 0; i < d; ++i)
+    for (int c = 0; c < kept; ++c) P[size_t(i) * k + c] = cols[size_t(c) * d + i];
   return kept;
 }
 
@@ -2112,6 +2120,7 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
   expmv_status status = EXPMV_OK;
   std::vector<double> Hh(size_t(ldh) * ldh);
   std::vector<double> rho(ns);
+  std::vector<double> zn_last(nt, 0.0);   // ||Z~_q|| of the last cycle
   // relaxed inner solves (opts.inner_relax = c > 0): the inner tolerance of
   // block j grows like rho_0 / rho_{j-1}, capped at 10^c (10^2 in the mixed
   // forms) times the base value
@@ -2181,6 +2190,35 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
     proj_solve(s, ns, d, p, precond ? 1 : 0, w.H, ldh, tau_re_d, tau_im_d, w.G, w.Ascr,
                w.Zs, w.Cr, ldx, w.S, w.rho, w.singular);
     double t1 = host_now_ms();
+    // When the estimates already say that this cycle does not converge (the
+    // rule below, with the last cycle's norms, or ||B||, for ||Z~||), the
+    // restart's eigenproblem starts on a host thread now, beside the X
+    // update, the residuals and the next cycle's first product
+    std::future<RestartCoords> coords;
+    auto start_restart = [&]() {
+      coords = std::async(std::launch::async, restart_coordinates, bool(pl->symmetric), precond, d,
+                          p, k, ldh, keff, kp, std::ref(Hh));
+    };
+    HIPCHK(hipMemcpyAsync(rho.data(), w.rho, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(Hh.data(), w.H, sizeof(double) * size_t(ldh) * ldh,
+                          hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (cycle < pl->opts.max_cycles && !inf.inner_maxit_hit) {
+      bool finite = true, more = false;
+      double rmax = 0.0;
+      for (int q = 0; q < nt; ++q) {
+        double bound = 0.0;
+        for (int j = 0; j < kNShift; ++j) {
+          const double r = rho[q * kNShift + j];
+          finite = finite && std::isfinite(r);
+          bound += cw[j] * r / delta[j];
+          rmax = std::max(rmax, r);
+        }
+        if (bound > tol * (cycle > 1 ? zn_last[q] : inf.bnorm)) more = true;
+      }
+      if (pl->opts.stop_rule == EXPMV_STOP_PAPER) more = rmax > tol * inf.bnorm;
+      if (finite && more) start_restart();
+    }
     // X_j += V_{d+p} (H~ Z_j)  [Algorithm 1: V_d Z_j]
     panel_gemm<T, double>(pl, p, Vb, d / p + 1, w.Cr, ldx, 2 * ns, w.X, p, ldx, 1);
     if (src && src->s_only)
@@ -2197,7 +2235,6 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
                            w.partial + size_t(cgrid) * q);
     HIPCHK(hipMemcpyAsync(part.data(), w.partial, sizeof(double) * cgrid * nt,
                           hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(rho.data(), w.rho, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
     int flags_h[4];
     HIPCHK(hipMemcpyAsync(flags_h, w.flags, sizeof(int) * 4, hipMemcpyDeviceToHost, s));
     std::vector<int> sing_h(ns);
@@ -2217,6 +2254,7 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
       for (int i = 0; i < cgrid; ++i) zz += part[size_t(cgrid) * q + i];
       zn_q[q] = std::sqrt(zz);
     }
+    zn_last = zn_q;
     double res_bound = 0.0, rem_bound = 0.0;
     for (int j = 0; j < kNShift; ++j) inf.true_res[j] = inf.noncollinear[j] = 0.0;
     for (int q = 0; q < nt; ++q) {
@@ -2290,11 +2328,7 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
     // from the eigensolve: it runs on the GPU while a host thread computes
     // the Ritz basis and the rotated H~.
     double t3 = host_now_ms();
-    HIPCHK(hipMemcpyAsync(Hh.data(), w.H, sizeof(double) * size_t(ldh) * ldh,
-                          hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    auto coords = std::async(std::launch::async, restart_coordinates, bool(pl->symmetric), precond,
-                             d, p, k, ldh, keff, kp, std::ref(Hh));
+    if (!coords.valid()) start_restart();
     const double ta = host_now_ms();
     apply_block(Vb + size_t(d / p) * blk);
     first_applied = true;
