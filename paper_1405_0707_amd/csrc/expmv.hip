@@ -1284,7 +1284,7 @@ SmallRadices small_radices(int64_t L, int most) {
 template <typename K, typename... Args>
 void launch_small_fft(expmv_plan_s* pl, K kernel, const SmallRadices& rad, int q, int cols,
                       Args... args) {
-  const size_t lds = sizeof(cplx) * size_t(rad.len) * (1 + cols);
+  const size_t lds = sizeof(cplx) * size_t(small_fft_at(rad.len) + 1) * (1 + cols);
   HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
   hipLaunchKernelGGL(kernel, dim3(q), dim3(kSmallFftThreads), lds, pl->stream, rad, args...);
@@ -1348,8 +1348,8 @@ void toeplitz_gsf_n(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, do
   // the second pair
   const cplx* g1 = tr ? pl->nsj.p : pl->ncx.p;
   const cplx* g2 = tr ? pl->nsz.p : pl->ncz.p;
-  // lengths that fit one workgroup's LDS: 48 us per call at n = 1,000, p = 2,
-  // against 154 for the 32 launches below (n = 3,000, p = 16: 91 and 163)
+  // lengths that fit one workgroup's LDS: 43 us per call at n = 1,000, p = 2,
+  // against 154 for the 32 launches below (n = 3,000, p = 16: 75 and 163)
   if (const SmallRadices sr = small_radices(n, kSmallFftInverse); sr.passes) {
     launch_small_fft(pl, k_small_gsf_n<T>, sr, q, 2, p, V, W, f1, f2, g1, g2,
                      transpose ? nullptr : di, transpose ? di : nullptr, tr ? 0.0 : -1.0,
@@ -1411,7 +1411,7 @@ void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, doub
   const cplx* b2 = tr ? gzjx : gzy;
   const int q = (p + 1) / 2;
   const int64_t L = pl->L, n = pl->n;
-  // (66 us per call at n = 1,001, p = 2, against 110)
+  // (52 us per call at n = 1,001, p = 2, against 110)
   if (const SmallRadices rad = small_radices(L, kSmallFftInverse); rad.passes) {
     launch_small_fft(pl, k_small_gsf<T>, rad, q, 2, int(n), p, V, W, a1, a2, b1, b2,
                      transpose ? nullptr : di, transpose ? di : nullptr, scale / pl->x0);

@@ -4,7 +4,7 @@
 //
 // The streaming passes of toeplitz.hpp cost one launch each, 2 to 3 us
 // whatever the length: at n = 1,000 an inverse took 32 launches and 154 us
-// for 16 KB of data (48 us here, 29 of them in the kernel; the source-term solve
+// for 16 KB of data (43 us here, 26 of them in the kernel; the source-term solve
 // 17.0 -> 11.9 ms).  Here a pass is a read of the column from LDS into
 // registers, a barrier and a write back in place (Stockham order), with the
 // roots of unity in an LDS table made once per launch.  The bound is the
@@ -20,9 +20,15 @@ namespace expmv {
 
 constexpr int kSmallFftThreads = 512;
 // Longest transforms.  An inverse keeps the table and two columns (48 bytes an
-// element) in 160 KB.  A product of length 4,096 took 36 us here and 29 in its
-// six streaming launches, of length 2,048 20 us and 27.
-constexpr int kSmallFftProduct = 2048, kSmallFftInverse = 3328;
+// element, 54 with the padding) in 160 KB.  A product of length 4,096 took 36 us
+// here and 29 in its six streaming launches, of length 2,048 15 us and 27.
+constexpr int kSmallFftProduct = 2048, kSmallFftInverse = 3000;
+
+// Place of element i of the table or a column in LDS: one element of padding
+// after every eight, so that the strided writes of the first passes (stride 8:
+// every lane on the same two groups of banks) spread over the banks: product of
+// length 2,048 19.4 -> 14.6 us, inverse at n = 1,001 66 -> 52 us
+__device__ __host__ inline int small_fft_at(int i) { return i + (i >> 3); }
 
 // A transform length as radices 8, 4, 2, 5, 3 in pass order (at most 7 passes
 // up to 3,328, reached by 3^7 = 2,187)
@@ -36,17 +42,18 @@ __device__ inline void small_fft_table(int L, cplx* tw) {
   for (int k = threadIdx.x; k < L; k += kSmallFftThreads) {
     double si, co;
     sincospi(-2.0 * double(k) / double(L), &si, &co);
-    tw[k] = {co, si};
+    tw[small_fft_at(k)] = {co, si};
   }
 }
 
-// One pass of radix R over NB columns at buf, buf + L (in place; the caller's
+// One pass of radix R over NB columns at buf, buf + column (in place; the caller's
 // data is visible to the workgroup on entry and on return).  The butterflies
 // of all columns are spread over the threads.
 template <int R, int NB>
 __device__ inline void small_fft_pass(int L, int Ns, const cplx* tw, cplx* buf, double sign) {
   static_assert(kSmallFftProduct <= kSmallFftInverse, "longest transform");
   constexpr int M = (NB * kSmallFftInverse / R + kSmallFftThreads - 1) / kSmallFftThreads;
+  const int column = small_fft_at(L) + 1;
   const int S = L / R, ts = S / Ns;   // ts: table step of w = exp(2 pi i / (Ns R))
   cplx V[M][R];
 #pragma unroll
@@ -56,15 +63,15 @@ __device__ inline void small_fft_pass(int L, int Ns, const cplx* tw, cplx* buf, 
     const cplx* x = buf;
     if (NB == 2 && j >= S) {
       j -= S;
-      x += L;
+      x += column;
     }
     const int k = j % Ns;
     cplx v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      v[r] = x[j + r * S];
+      v[r] = x[small_fft_at(j + r * S)];
       if (r > 0) {
-        const cplx w = tw[r * k * ts];   // r k < R Ns: below L
+        const cplx w = tw[small_fft_at(r * k * ts)];   // r k < R Ns: below L
         v[r] = cmul(v[r], cplx{w.x, -sign * w.y});
       }
     }
@@ -78,12 +85,12 @@ __device__ inline void small_fft_pass(int L, int Ns, const cplx* tw, cplx* buf, 
     cplx* x = buf;
     if (NB == 2 && j >= S) {
       j -= S;
-      x += L;
+      x += column;
     }
     const int k = j % Ns;
     const int d = (j - k) * R + k;
 #pragma unroll
-    for (int r = 0; r < R; ++r) x[d + r * Ns] = V[m][r];
+    for (int r = 0; r < R; ++r) x[small_fft_at(d + r * Ns)] = V[m][r];
   }
   __syncthreads();
 }
@@ -128,20 +135,21 @@ k_small_toeplitz(SmallRadices rad, int n, int p, const T* X, int64_t ldx,
   extern __shared__ char fft_lds[];
   const int L = rad.len, c = blockIdx.x;
   cplx* tw = reinterpret_cast<cplx*>(fft_lds);
-  cplx* buf = tw + L;
+  cplx* buf = tw + small_fft_at(L) + 1;
   small_fft_table(L, tw);
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads)
-    buf[i] = i < n ? small_pair(X, ldx, p, c, i, din) : cplx{0.0, 0.0};
+    buf[small_fft_at(i)] = i < n ? small_pair(X, ldx, p, c, i, din) : cplx{0.0, 0.0};
   __syncthreads();
   small_fft<1>(rad, tw, buf, -1.0);
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads) {
-    const cplx v = cmul(buf[i], sym[i]);
-    buf[i] = {scale * v.x, scale * v.y};
+    cplx& b = buf[small_fft_at(i)];
+    const cplx v = cmul(b, sym[i]);
+    b = {scale * v.x, scale * v.y};
   }
   __syncthreads();
   small_fft<1>(rad, tw, buf, 1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads)
-    small_unpair(Y, ldy, p, c, i, dout ? dout[i] : 1.0, buf[i]);
+    small_unpair(Y, ldy, p, c, i, dout ? dout[i] : 1.0, buf[small_fft_at(i)]);
 }
 
 // The length-n Gohberg-Semencul inverse (toeplitz_gsf_n: the same factors in
@@ -157,38 +165,41 @@ k_small_gsf_n(SmallRadices rad, int p, const T* V, T* W,
   extern __shared__ char fft_lds[];
   const int n = rad.len, c = blockIdx.x;
   cplx* tw = reinterpret_cast<cplx*>(fft_lds);
-  cplx* buf = tw + n;   // two columns
+  cplx* buf = tw + small_fft_at(n) + 1;   // two columns
+  cplx* buf2 = buf + small_fft_at(n) + 1;
   const double inv = 1.0 / double(n);
   small_fft_table(n, tw);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads) {
     const cplx v = small_pair(V, p, p, c, i, din);
-    buf[i] = first != 0.0 ? cmul(v, twist_factor(i, n, first)) : v;
+    buf[small_fft_at(i)] = first != 0.0 ? cmul(v, twist_factor(i, n, first)) : v;
   }
   __syncthreads();
   small_fft<1>(rad, tw, buf, -1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads) {
-    const int m = i == 0 ? 0 : n - i;
-    const cplx u = buf[i], a = cmul(u, f1[m]), b = cmul(u, f2[m]);
-    buf[i] = {inv * a.x, inv * a.y};
-    buf[n + i] = {inv * b.x, inv * b.y};
+    const int m = i == 0 ? 0 : n - i, at = small_fft_at(i);
+    const cplx u = buf[at], a = cmul(u, f1[m]), b = cmul(u, f2[m]);
+    buf[at] = {inv * a.x, inv * a.y};
+    buf2[at] = {inv * b.x, inv * b.y};
   }
   __syncthreads();
   small_fft<2>(rad, tw, buf, 1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads) {
     const cplx t = twist_factor(i, n, 1.0);
-    buf[i] = cmul(buf[i], t);
-    buf[n + i] = cmul(buf[n + i], t);
+    const int at = small_fft_at(i);
+    buf[at] = cmul(buf[at], t);
+    buf2[at] = cmul(buf2[at], t);
   }
   __syncthreads();
   small_fft<2>(rad, tw, buf, -1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads) {
-    const cplx a = cmul(buf[i], g1[i]), b = cmul(buf[n + i], g2[i]);
-    buf[i] = {inv * (a.x - b.x), inv * (a.y - b.y)};
+    const int at = small_fft_at(i);
+    const cplx a = cmul(buf[at], g1[i]), b = cmul(buf2[at], g2[i]);
+    buf[at] = {inv * (a.x - b.x), inv * (a.y - b.y)};
   }
   __syncthreads();
   small_fft<1>(rad, tw, buf, 1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads) {
-    cplx v = buf[i];
+    cplx v = buf[small_fft_at(i)];
     if (last != 0.0) v = cmul(v, twist_factor(i, n, last));
     small_unpair(W, p, p, c, i, dout ? scale * dout[i] : scale, v);
   }
@@ -205,43 +216,47 @@ k_small_gsf(SmallRadices rad, int n, int p, const T* V, T* W,
   extern __shared__ char fft_lds[];
   const int L = rad.len, c = blockIdx.x;
   cplx* tw = reinterpret_cast<cplx*>(fft_lds);
-  cplx* buf = tw + L;   // two columns
+  cplx* buf = tw + small_fft_at(L) + 1;   // two columns
+  cplx* buf2 = buf + small_fft_at(L) + 1;
   const double inv = 1.0 / double(L);
   small_fft_table(L, tw);
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads)
-    buf[i] = i < n ? small_pair(V, p, p, c, n - 1 - i, din) : cplx{0.0, 0.0};
+    buf[small_fft_at(i)] = i < n ? small_pair(V, p, p, c, n - 1 - i, din) : cplx{0.0, 0.0};
   __syncthreads();
   small_fft<1>(rad, tw, buf, -1.0);
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads) {
-    const cplx u = buf[i], a = cmul(u, a1[i]), b = cmul(u, a2[i]);
-    buf[i] = {inv * a.x, inv * a.y};
-    buf[L + i] = {inv * b.x, inv * b.y};
+    const int at = small_fft_at(i);
+    const cplx u = buf[at], a = cmul(u, a1[i]), b = cmul(u, a2[i]);
+    buf[at] = {inv * a.x, inv * a.y};
+    buf2[at] = {inv * b.x, inv * b.y};
   }
   __syncthreads();
   small_fft<2>(rad, tw, buf, 1.0);
   // reversed in place and cut to n rows
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads) {
-    const int m = n - 1 - i;
+    const int m = n - 1 - i, at = small_fft_at(i);
     if (i < m) {
-      const cplx a = buf[i], b = buf[L + i];
-      buf[i] = buf[m];
-      buf[m] = a;
-      buf[L + i] = buf[L + m];
-      buf[L + m] = b;
+      const int am = small_fft_at(m);
+      const cplx a = buf[at], b = buf2[at];
+      buf[at] = buf[am];
+      buf[am] = a;
+      buf2[at] = buf2[am];
+      buf2[am] = b;
     } else if (i >= n) {
-      buf[i] = buf[L + i] = {0.0, 0.0};
+      buf[at] = buf2[at] = {0.0, 0.0};
     }
   }
   __syncthreads();
   small_fft<2>(rad, tw, buf, -1.0);
   for (int i = threadIdx.x; i < L; i += kSmallFftThreads) {
-    const cplx a = cmul(buf[i], b1[i]), b = cmul(buf[L + i], b2[i]);
-    buf[i] = {inv * (a.x - b.x), inv * (a.y - b.y)};
+    const int at = small_fft_at(i);
+    const cplx a = cmul(buf[at], b1[i]), b = cmul(buf2[at], b2[i]);
+    buf[at] = {inv * (a.x - b.x), inv * (a.y - b.y)};
   }
   __syncthreads();
   small_fft<1>(rad, tw, buf, 1.0);
   for (int i = threadIdx.x; i < n; i += kSmallFftThreads)
-    small_unpair(W, p, p, c, i, dout ? scale * dout[i] : scale, buf[i]);
+    small_unpair(W, p, p, c, i, dout ? scale * dout[i] : scale, buf[small_fft_at(i)]);
 }
 
 }  // namespace expmv

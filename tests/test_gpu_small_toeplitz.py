@@ -28,10 +28,10 @@ def vectors(n, symmetric):
     return col, (col if symmetric else row)
 
 
-# inverse: radices 2 3 4 5 8, lengths 3^7, 5^5, the last one in LDS (3,240 = 2^3 3^4
-# 5) and the first past it (3,375); embedding form below and above n = 1,024;
+# inverse: radices 2 3 4 5 8, lengths 3^7, the last one in LDS (3,000) and some past
+# it; embedding form below and above n = 1,024;
 # product: L = 2,048 at n = 1,024, past it at 1,025
-SIZES = [2, 3, 5, 8, 30, 97, 625, 1000, 1009, 1024, 1025, 2048, 2049, 2187, 3125, 3240, 3375]
+SIZES = [2, 3, 5, 8, 30, 97, 625, 1000, 1009, 1024, 1025, 2048, 2049, 2187, 3000, 3125, 3240, 3375]
 
 
 @pytest.mark.parametrize("n", SIZES)
