@@ -1522,6 +1522,30 @@ int orth_pass(expmv_plan_s* pl, int mode, int p, const T* V, int npan, const T* 
       ev = kt_take(pl, EXPMV_KT_ORTH, el * (mode == kProj ? npv + 1 : (upd ? npv + 2 : 2)));
     }
     hipEvent_t e0 = ev.e0, e1 = ev.e1;
+    if constexpr (std::is_same<T, double>::value) {
+      // update passes of an FP64 basis of panels of 16 or 8 columns: two
+      // workgroups of eight wavefronts per CU
+      if (upd && npv > 0 && (p == 16 || p == 8)) {
+        grid = int(std::min<int64_t>(2 * kCUs, (pl->n + 15) / 16));
+        auto launch = [&](auto kernel) {
+          hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kOrthUpdThreads), 0, pl->stream, e0, e1, 0,
+                                pl->n, V, npv, Win, Wout, C, pl->ws.partial);
+        };
+#define ORTH_UPD(MB_)                                   \
+  do {                                                  \
+    if (p == 16 && gram) launch(k_orth_upd<true, MB_, 16>);  \
+    else if (p == 16) launch(k_orth_upd<false, MB_, 16>);    \
+    else if (gram) launch(k_orth_upd<true, MB_, 8>);    \
+    else launch(k_orth_upd<false, MB_, 8>);             \
+  } while (0)
+        if (nmb <= 8) ORTH_UPD(1);
+        else if (nmb <= 16) ORTH_UPD(2);
+        else if (nmb <= 24) ORTH_UPD(3);
+        else ORTH_UPD(4);
+#undef ORTH_UPD
+        return grid;
+      }
+    }
 #define ORTH_MMA(NB_, MBW_)                                                                     \
   do {                                                                                          \
     grid = orth_mma_grid(orth_mma_lds<T, NB_, MBW_>(), steps);                                  \

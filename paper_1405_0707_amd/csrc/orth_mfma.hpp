@@ -371,4 +371,151 @@ k_panel_gemm_mma(int64_t n, int p_arg, const T* __restrict__ V, int npan,
   }
 }
 
+// The update passes (kUpdProj, kUpdGram) of an FP64 basis with p <= 16 columns
+// per panel.  k_orth_mma splits the rows over its wavefronts for the update and
+// the basis columns for the projection, so that it reads V twice (counted: 1.97
+// times V at 17 panels; the second time from the 256 MB cache) and C once per 16
+// rows.  Here eight wavefronts take 16 rows per step and own the column blocks
+// wave, wave + 8, ... throughout: their part of C and their projection sums stay
+// in registers, and a block of V is loaded once, in both operand layouts (the
+// second after the first is used, from the cache).  Per step the wavefronts' parts of V C meet
+// in LDS (two buffers, one barrier) and each forms W' for itself.  Same products
+// in FP64; the sum over basis columns is grouped by wavefront.  Bound: memory.
+// At n = 2^20, p = 16 (2.4 GB at 16 panels): projecting update 865 -> 612 us and
+// Gram update 663 -> 471 at 16 panels, 963 -> 880 and 721 -> 531 at 17; with p = 8
+// at 64^3 the pass sum goes from 3.8 to 3.5 ms per solve.
+// MB = column blocks per wavefront (npan p <= 128 MB); PC = p = 16 or 8 (a
+// column block is one panel or two).  The projecting update takes 146 and 178
+// registers at MB = 3 and 4, hence one workgroup per CU (at two it spills: 972 us
+// at 17 panels); all others run two.
+// W and Wout may be the same array (only wavefront 0 reads W, before the
+// barrier that the stores come after).
+constexpr int kOrthUpdThreads = 512;
+template <bool GRAM, int MB, int PC>
+__global__ void __launch_bounds__(kOrthUpdThreads, (!GRAM && MB > 2) ? 2 : 4)
+k_orth_upd(int64_t n, const double* __restrict__ V, int npan, const double* W, double* Wout,
+           const double* __restrict__ C, double* __restrict__ partial) {
+  using M = Mma<double>;
+  using v4 = typename M::v4;
+  constexpr int NW = kOrthUpdThreads / 64, p = PC;
+  __shared__ double part[2][NW][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int np_cols = npan * p, nmb = (np_cols + 15) / 16;
+  double cf[MB][4];
+  v4 acc[MB], g = v4{0, 0, 0, 0};
+#pragma unroll
+  for (int u = 0; u < MB; ++u) {
+    acc[u] = v4{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kc = 16 * (wave + NW * u) + 4 * lk + s;
+      cf[u][s] = (kc < np_cols && li < p) ? C[int64_t(kc) * p + li] : 0.0;
+    }
+  }
+  const int64_t steps = (n + 15) / 16;
+  int buf = 0;
+  for (int64_t st = blockIdx.x; st < steps; st += gridDim.x, buf ^= 1) {
+    const int64_t r0 = 16 * st;
+    const int64_t rowa = r0 + li < n ? r0 + li : n - 1;
+    double x[MB][4];
+#pragma unroll
+    for (int u = 0; u < MB; ++u) {
+      const int mb = wave + NW * u;
+      if (mb >= nmb) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[u][s] = 0.0;
+        continue;
+      }
+      // columns 16 mb + 4 lk .. + 3 of row rowa: one 32-byte run of a panel (a
+      // last half block, PC = 8, is clamped; its part of C is zero)
+      const int ca = min(16 * mb + 4 * lk, np_cols - 4);
+      const double2* src =
+          reinterpret_cast<const double2*>(V + (int64_t(ca / PC) * n + rowa) * PC + ca % PC);
+      const double2 y0 = src[0], y1 = src[1];
+      x[u][0] = y0.x;
+      x[u][1] = y0.y;
+      x[u][2] = y1.x;
+      x[u][3] = y1.y;
+    }
+    v4 d = v4{0, 0, 0, 0};
+    double w[4] = {0.0, 0.0, 0.0, 0.0};
+    if (wave == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = r0 + lk + 4 * r;
+        if (row < n && li < p) w[r] = W[row * p + li];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < MB; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) d = M::mma(x[u][s], cf[u][s], d);
+    // the second layout only now, in the same registers: its latency overlaps
+    // the exchange through LDS
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!GRAM) {
+#pragma unroll
+      for (int u = 0; u < MB; ++u) {
+        const int mb = wave + NW * u;
+        if (mb >= nmb) continue;
+        const int col = min(16 * mb + li, np_cols - 1);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int64_t row = r0 + lk + 4 * s;
+          x[u][s] = basis_at(V, n, p, row < n ? row : n - 1, col);
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[buf][wave][r][lane] = w[r] - d[r];
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double s = part[buf][0][r][lane];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) s += part[buf][q][r][lane];
+      const int64_t row = r0 + lk + 4 * r;
+      const bool in = row < n && li < p;
+      w[r] = in ? s : 0.0;
+      if (in && wave == r) Wout[row * p + li] = s;
+    }
+    if constexpr (GRAM) {
+      if (((st / gridDim.x) & (NW - 1)) == wave) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) g = M::mma(w[s], w[s], g);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < MB; ++u)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[u] = M::mma(x[u][s], w[s], acc[u]);
+    }
+  }
+  if constexpr (GRAM) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[0][wave][r][lane] = g[r];
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double s = part[0][0][r][lane];
+        for (int q = 1; q < NW; ++q) s += part[0][q][r][lane];
+        const int i = lk + 4 * r;
+        if (i < p && li < p) partial[size_t(blockIdx.x) * p * p + i * p + li] = s;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < MB; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int col = 16 * (wave + NW * u) + lk + 4 * r;
+        if (col < np_cols && li < p)
+          partial[size_t(blockIdx.x) * np_cols * p + size_t(col) * p + li] = acc[u][r];
+      }
+  }
+}
+
 }  // namespace expmv
