@@ -2008,6 +2008,13 @@ InnerResult apply_inverse_mixed(expmv_plan_s* pl, int transpose, const T* V, T* 
 void proj_solve(hipStream_t s, int ns, int d, int p, int precond, const double* H, int ldh,
                 const double* tau_re, const double* tau_im, const cplx* G, cplx* Ascr, cplx* Zs,
                 double* Cr, int ldc, cplx* S, double* rho, int* singular) {
+  if (const size_t lds = proj_small_lds(d, p); d <= 96 && lds <= kProjSmallLds) {
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_proj_solve_small),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    hipLaunchKernelGGL(k_proj_solve_small, dim3(ns), dim3(kProjSmallThreads), lds, s, d, p, precond,
+                       H, ldh, tau_re, tau_im, G, Cr, ldc, S, rho, singular);
+    return;
+  }
   hipLaunchKernelGGL(k_proj_solve, dim3(ns), dim3(1024), 0, s, d, p, precond, H, ldh, tau_re,
                      tau_im, G, Ascr, Zs, Cr, ldc, S, rho, singular);
 }

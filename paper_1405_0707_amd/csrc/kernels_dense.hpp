@@ -531,6 +531,190 @@ k_proj_solve(int d, int p, int precond, const double* __restrict__ H, int ldh,
   }
 }
 
+// k_proj_solve with the whole system in LDS (A at a row stride of d + 1, which
+// spreads its columns over the banks, Z and the reciprocals of U's diagonal) and
+// four wavefronts: the same elimination, pivots and band limit, without an L2
+// round trip per step.  Bound: the chain of a column's pivot search, reciprocal
+// and barriers (about 1 us).  Mean per call over a solve: 32^2, p = 4 (d <= 40)
+// 79 -> 50 us, 12^3, p = 3 (d <= 30) 64 -> 40, 320^2, p = 8 (d <= 80) 177 -> 128.
+constexpr int kProjSmallThreads = 256;
+constexpr size_t kProjSmallLds = 150 * 1024;
+inline size_t proj_small_lds(int d, int p) {
+  return sizeof(cplx) * (size_t(d) * (d + 1) + size_t(d) * p + size_t(d));
+}
+__global__ void __launch_bounds__(kProjSmallThreads)
+k_proj_solve_small(int d, int p, int precond, const double* __restrict__ H, int ldh,
+                   const double* __restrict__ tau_re, const double* __restrict__ tau_im,
+                   const cplx* __restrict__ G, double* __restrict__ Cr, int ldc,
+                   cplx* __restrict__ S, double* __restrict__ rho, int* __restrict__ singular) {
+  extern __shared__ char proj_lds[];
+  constexpr int nt = kProjSmallThreads;
+  const int j = blockIdx.x, tid = threadIdx.x, ld = d + 1;
+  cplx* A = reinterpret_cast<cplx*>(proj_lds);
+  cplx* Z = A + size_t(d) * ld;
+  cplx* sInv = Z + size_t(d) * p;
+  __shared__ int s_piv, s_zero, s_lim[128];
+  __shared__ cplx s_inv;
+  __shared__ double s_rho[nt / 64];
+  const cplx tau{tau_re[j], tau_im[j]};
+  for (int c = tid; c < d; c += nt) s_lim[c] = c;
+  __syncthreads();
+  for (int idx = tid; idx < d * d; idx += nt) {
+    const int r = idx / d, c = idx % d;
+    const double h = H[int64_t(r) * ldh + c];
+    if (r > c && h != 0.0) atomicMax(&s_lim[c], r);
+    cplx a;
+    if (precond) {
+      a = {-tau.x * h, -tau.y * h};
+      if (r == c) a.x += 1.0;
+    } else {
+      a = {h, 0.0};
+      if (r == c) {
+        a.x -= tau.x;
+        a.y -= tau.y;
+      }
+    }
+    A[r * ld + c] = a;
+  }
+  for (int idx = tid; idx < d * p; idx += nt) Z[idx] = G[size_t(j) * d * p + idx];
+  __syncthreads();
+  if (tid == 0)
+    for (int c = 1; c < d; ++c) s_lim[c] = max(s_lim[c], s_lim[c - 1]);
+  __syncthreads();
+  int sing = 0;
+  for (int c = 0; c < d; ++c) {
+    const int last = s_lim[c];
+    if (tid < 64) {
+      double best = -1.0;
+      int bi = c;
+      for (int r = c + tid; r <= last; r += 64) {
+        const cplx a = A[r * ld + c];
+        const double v = a.x * a.x + a.y * a.y;
+        if (v > best) {
+          best = v;
+          bi = r;
+        }
+      }
+      // lanes past the column's rows hold -1
+      int off = 1;
+      while (off < last - c + 1 && off < 64) off <<= 1;
+      for (off >>= 1; off >= 1; off >>= 1) {
+        const double ob = __shfl_xor(best, off, 64);
+        const int oi = __shfl_xor(bi, off, 64);
+        if (ob > best || (ob == best && oi < bi)) {
+          best = ob;
+          bi = oi;
+        }
+      }
+      if (tid == 0) {
+        s_piv = bi;
+        s_zero = !(best > 0.0);
+        s_inv = best > 0.0 ? cdiv(cplx{1.0, 0.0}, A[bi * ld + c]) : cplx{0.0, 0.0};
+      }
+    }
+    __syncthreads();
+    const int pv = s_piv;
+    if (s_zero) {
+      sing = 1;
+      __syncthreads();
+      continue;
+    }
+    const int m1 = d - c - 1, wide = m1 + p;
+    if (pv != c) {
+      for (int i = tid; i < wide + 1; i += nt) {
+        cplx *x, *y;
+        if (i <= m1) {
+          x = &A[c * ld + c + i];
+          y = &A[pv * ld + c + i];
+        } else {
+          x = &Z[c * p + i - m1 - 1];
+          y = &Z[pv * p + i - m1 - 1];
+        }
+        const cplx t = *x;
+        *x = *y;
+        *y = t;
+      }
+      __syncthreads();
+    }
+    const cplx inv = s_inv;
+    const int rows = last - c;
+    for (int idx = tid; idx < rows * wide; idx += nt) {
+      const int r = c + 1 + idx / wide, cc = idx % wide;
+      const cplx l = cmul(A[r * ld + c], inv);
+      if (cc < m1) {
+        const int col = c + 1 + cc;
+        A[r * ld + col] = csub(A[r * ld + col], cmul(l, A[c * ld + col]));
+      } else {
+        const int b = cc - m1;
+        Z[r * p + b] = csub(Z[r * p + b], cmul(l, Z[c * p + b]));
+      }
+    }
+    __syncthreads();
+  }
+  for (int c = tid; c < d; c += nt) {
+    const cplx dg = A[c * ld + c];
+    sInv[c] = (dg.x == 0.0 && dg.y == 0.0) ? cplx{0.0, 0.0} : cdiv(cplx{1.0, 0.0}, dg);
+  }
+  __syncthreads();
+  // back substitution: every thread forms x_c itself; row c of Z is overwritten
+  // by it one step later, when no thread reads it any more
+  auto xval = [&](int c, int b) -> cplx { return cmul(Z[c * p + b], sInv[c]); };
+  const int rstep = nt / p, tr = tid / p, tb = tid % p;
+  for (int c = d - 1; c >= 0; --c) {
+    cplx xn{0.0, 0.0};
+    const bool wr = c + 1 < d && tid < p;
+    if (wr) xn = xval(c + 1, tid);
+    if (tr < rstep) {
+      const cplx x = xval(c, tb);
+      for (int r = tr; r < c; r += rstep)
+        Z[r * p + tb] = csub(Z[r * p + tb], cmul(A[r * ld + c], x));
+    }
+    if (wr) Z[(c + 1) * p + tid] = xn;
+    __syncthreads();
+  }
+  if (tid < p) Z[tid] = xval(0, tid);
+  __syncthreads();
+  if (tid == 0 && sing) singular[j] = 1;
+  // Cr as in k_proj_solve (rows d .. d + p - 1 are also S_j / tau)
+  for (int idx = tid; Cr && idx < (d + p) * p; idx += nt) {
+    const int r = idx / p, b = idx % p;
+    cplx s{0.0, 0.0};
+    if (precond) {
+#pragma unroll 8
+      for (int c = 0; c < d; ++c) {
+        const double h = H[int64_t(r) * ldh + c];
+        const cplx z = Z[c * p + b];
+        s.x += h * z.x;
+        s.y += h * z.y;
+      }
+    } else if (r < d) {
+      s = Z[r * p + b];
+    }
+    Cr[int64_t(r) * ldc + 2 * p * j + b] = s.x;
+    Cr[int64_t(r) * ldc + 2 * p * j + p + b] = s.y;
+  }
+  double ss = 0.0;
+  for (int idx = tid; idx < p * p; idx += nt) {
+    const int a = idx / p, b = idx % p;
+    cplx s{0.0, 0.0};
+#pragma unroll 8
+    for (int c = 0; c < d; ++c) {
+      const double h = H[int64_t(d + a) * ldh + c];
+      const cplx z = Z[c * p + b];
+      s.x += h * z.x;
+      s.y += h * z.y;
+    }
+    const cplx v = precond ? cmul(tau, s) : cplx{-s.x, -s.y};
+    S[size_t(j) * p * p + idx] = v;
+    ss += v.x * v.x + v.y * v.y;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+  if (tid % 64 == 0) s_rho[tid / 64] = ss;
+  __syncthreads();
+  if (tid == 0) rho[j] = sqrt((s_rho[0] + s_rho[1]) + (s_rho[2] + s_rho[3]));
+}
+
 // Right-hand sides of the projected systems: G_j = 0 except rows
 // row0..row0+p-1 = src (cycle 1: src = R^ real p x p, same for all j;
 // after a restart: src = S_j complex).
