@@ -595,7 +595,7 @@ void toeplitz_apply(expmv_plan_s* pl, const T* X, int64_t ldx, T* Y, int64_t ldy
 template <typename T>
 void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, double scale);
 
-int cg_grid(int64_t n, int PP);
+int cg_grid(int64_t n, int PP, int p);
 
 // Whether the SpMMs stage the operator's entries through LDS (spmm_rows).
 int staged_rows(const expmv_plan_s* pl) { return pl->nnz <= 8 * pl->n ? 1 : 0; }
@@ -610,7 +610,7 @@ void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double sc
   Csr<T> A = csr_of<T>(pl, transpose);
   const int PP = pow2_lanes(p);
   DISPATCH_PP(PP, SPMM_DISPATCH(T, P_, p,
-                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(cg_grid(pl->n, PP)),
+                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(cg_grid(pl->n, PP, p)),
                                                    dim3(kCgThreads), 0, pl->stream, int(pl->n), p,
                                                    A.rowptr, A.colind, A.val, staged_rows(pl), X, Y,
                                                    scale)));
@@ -663,10 +663,17 @@ struct InnerResult {
   int hit_cap;
 };
 
-int cg_grid(int64_t n, int PP) {
-  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(kCgGrid, (n * PP + 1023) / 1024));
+// Workgroups (of kCgThreads) that take n rows of `lanes` lanes in one pass, at
+// most kCgGrid, a multiple of 8 from 8 on (xcd_rows, StreamRows).
+int grid_lanes(int64_t n, int lanes) {
+  const int64_t g = std::max<int64_t>(
+      1, std::min<int64_t>(kCgGrid, (n * lanes + kCgThreads - 1) / kCgThreads));
   return int(g < 8 ? g : (g + 7) / 8 * 8);
 }
+
+// Grid of the inner-solver kernels for p columns (PP = p rounded up to a power
+// of two): two columns per lane when p is even.
+int cg_grid(int64_t n, int PP, int p) { return grid_lanes(n, p % 2 == 0 ? PP / 2 : PP); }
 
 double inner_tol_of(expmv_plan_s* pl) {
   const double base = pl->opts.inner_tol > 0.0 ? pl->opts.inner_tol : (pl->mixed ? 1e-6 : 1e-12);
@@ -818,7 +825,7 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
     launch_pair(G, e, xc);
     return;
   }
-  const int gfine = cg_grid(n, PP);
+  const int gfine = cg_grid(n, PP, p);
   const int GA = row_split(L.avg_a, PPL), GP = row_split(L.avg_p, PPL);
   const int gcoarse_a = grid_amg(n, PPL * GA), gcoarse_p = grid_amg(n, PPL * GP);
   // one smoothing step: reads A, D^{-1}, b and the iterate (unless it is the
@@ -867,7 +874,7 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
                                            blk);
     const int G = std::max(GA, GP);
     hipExtLaunchKernelGGL((k_amg_affine_pair<T, PPL, VW, kCgThreads, true>),
-                          dim3(cg_grid(n, 2 * PPL * G)), dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k,
+                          dim3(grid_lanes(n, PPL * G)), dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k,
                           ctl, n, p, G, L.arp, L.aci, lv.a, dinv, b, L.Prp.p, L.Pci.p, lv.p, xc, L.alpha, L.beta,
                           x);
   } else {
@@ -1032,7 +1039,7 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
   hipStream_t s = pl->stream;
   const int64_t n = pl->n;
   const int PP = pow2_lanes(p);
-  const int grid = cg_grid(n, PP);
+  const int grid = cg_grid(n, PP, p);
   const double tol = inner_tol_of(pl);
   const double tol2 = tol * tol;
   const int maxit = pl->opts.inner_maxit;
@@ -1129,7 +1136,7 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
   hipStream_t s = pl->stream;
   const int64_t n = pl->n;
   const int PP = pow2_lanes(p);
-  const int grid = cg_grid(n, PP);
+  const int grid = cg_grid(n, PP, p);
   const double tol = inner_tol_of(pl);
   const double tol2 = tol * tol;
   const int maxit = pl->opts.inner_maxit;

@@ -190,6 +190,16 @@ __device__ inline void reduce_parts(const double* __restrict__ part, int nwg, do
   if (sidx < slots) {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     int w = l;
+    // up to eight partials per thread in one round trip (512 workgroups)
+    for (; w + 7 * lanes < nwg; w += 8 * lanes) {
+      double b[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) b[u] = part[size_t(w + u * lanes) * slots + sidx];
+      a0 += b[0] + b[4];
+      a1 += b[1] + b[5];
+      a2 += b[2] + b[6];
+      a3 += b[3] + b[7];
+    }
     for (; w + 3 * lanes < nwg; w += 4 * lanes) {
       a0 += part[size_t(w) * slots + sidx];
       a1 += part[size_t(w + lanes) * slots + sidx];
