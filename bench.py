@@ -42,7 +42,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # block Arnoldi steps per cycle of the 128^3 workload (k = p floor(m / 3) = 128):
 # the configuration leaves m open; m = 24 needs 5 cycles and 4.0 s, m = 20 7
-# cycles and 4.5 s, m = 28 4 cycles and 4.0 s (mixed form 1.65, 1.92, 2.00 s),
+# cycles and 4.5 s, m = 28 4 cycles and 4.0 s (mixed form 1.65, 1.92, 2.00 s; 3.6
+# and 1.5 s at m = 24 with the staged products),
 # with the same accuracy against the oracle
 C4_M = 24
 # block steps per cycle of the 1024^2 workload: both forms converge within one
