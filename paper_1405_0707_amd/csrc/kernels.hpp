@@ -15,6 +15,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "host_rules.hpp"
+
 namespace expmv {
 
 constexpr int kThreads = 256;
@@ -453,9 +455,9 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
   auto fetch = [&](int b, int e) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const int i = b + tid + s * NT;
-      js[s] = i < e ? colind[i] : 0;
-      vs[s] = i < e ? val[i] : 0.0;
+      const int i = tid + s * NT;
+      js[s] = i < e - b ? colind[b + i] : 0;
+      vs[s] = i < e - b ? val[b + i] : 0.0;
     }
   };
   auto extents = [&](int64_t r, int& a, int& b) {
@@ -465,7 +467,7 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
       b = rowptr[r + 1];
     }
   };
-  fetch(cb, min(cb + CH, tb));
+  fetch(cb, chunk_end(cb, tb, CH));
   int e0, e1, ne0, ne1;
   extents(row, e0, e1);
   extents(row + TR, ne0, ne1);
@@ -473,17 +475,17 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
 #pragma unroll
   for (int q = 0; q < VW; ++q) acc[q] = 0.0;
   for (int buf = 0;; buf ^= CH) {
-    const int ce = min(cb + CH, tb);
+    const int ce = chunk_end(cb, tb, CH);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int i = tid + s * NT;
-      if (cb + i < ce) {
+      if (i < ce - cb) {
         sj[buf + i] = js[s];
         sv[buf + i] = vs[s];
       }
     }
     const bool last = ce >= tb;
-    fetch(ce, min(ce + CH, last ? tn : tb));
+    fetch(ce, chunk_end(ce, last ? tn : tb, CH));
     lds_barrier();
     const int lo = max(e0, cb) - cb + buf, hi = min(e1, ce) - cb + buf;
     for (int e = lo; e < hi; e += U) {
