@@ -26,6 +26,7 @@
 #include "amg_host.hpp"
 #include "eig_host.hpp"
 #include "expmv.h"
+#include "host_rules.hpp"
 #include "kernels.hpp"
 #include "kernels_dense.hpp"
 #include "orth_mfma.hpp"
@@ -290,6 +291,20 @@ constexpr int kCUs = 256;
 constexpr size_t kLdsPerCU = 160 * 1024;
 constexpr int64_t kAmgFusedMax = int64_t(1) << 21;   // entries of the fused Inv R (16 MB)
 constexpr int kMaxTimes = 32;  // times of one expmv_execute_times call
+
+// Let `kernel` be launched with all the LDS that its static arrays leave free.
+// The limit belongs to the function, not to a plan: set to each launch's own
+// size, one plan could lower it between another thread's setting and launch.
+void allow_dynamic_lds(const void* kernel) {
+  int device = 0;
+  HIPCHK(hipGetDevice(&device));
+  once_per_kernel(kernel, device, [&]() {
+    hipFuncAttributes attr{};
+    HIPCHK(hipFuncGetAttributes(&attr, kernel));
+    HIPCHK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               int(kLdsPerCU - attr.sharedSizeBytes)));
+  });
+}
 
 int grid_for(int64_t rows, int PP, int cap = 1024) {
   const int64_t wgs = (rows * PP + kThreads - 1) / kThreads;
@@ -993,8 +1008,7 @@ InnerResult run_small_solve(expmv_plan_s* pl, int transpose, const T* src, doubl
                                    : reinterpret_cast<SmallResult*>(w.bcgst);
   auto launch = [&](auto kernel, int nt, int rows, int nred, int nvec) {
     const size_t lds = sizeof(double) * nred * (nt / 64) + sizeof(T) * size_t(nvec) * nt * rows;
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    allow_dynamic_lds(reinterpret_cast<const void*>(kernel));
     hipLaunchKernelGGL(kernel, dim3(p), dim3(nt), lds, s, n, p, sign, A.rowptr, A.colind, A.val,
                        A.dinv, src, out, tol * tol, pl->opts.inner_maxit, res);
   };
@@ -1292,8 +1306,7 @@ template <typename K, typename... Args>
 void launch_small_fft(expmv_plan_s* pl, K kernel, const SmallRadices& rad, int q, int cols,
                       Args... args) {
   const size_t lds = sizeof(cplx) * size_t(small_fft_at(rad.len) + 1) * (1 + cols);
-  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel));
   hipLaunchKernelGGL(kernel, dim3(q), dim3(kSmallFftThreads), lds, pl->stream, rad, args...);
 }
 
@@ -1580,8 +1593,7 @@ int orth_pass(expmv_plan_s* pl, int mode, int p, const T* V, int npan, const T* 
     return (proj || gram) ? grid : 0;
   }
   OrthLaunch L = orth_config(pl->n, p, npv, O, sizeof(T));
-  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_orth<T>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(L.lds)));
+  allow_dynamic_lds(reinterpret_cast<const void*>(&k_orth<T>));
   hipLaunchKernelGGL(k_orth<T>, dim3(L.nwg), dim3(kThreads), L.lds, pl->stream, mode, pl->n, p, V,
                      npv, Win, Wout, C, pl->ws.partial, L.TR, L.rows_per_wg, gate);
   return (proj || gram) ? L.nwg : 0;
@@ -1678,8 +1690,7 @@ void orthonormalize(expmv_plan_s* pl, int p, const T* Vb, int npan, T* W, T* Vou
   if (small_orth(pl, p, npan)) {
     const size_t lds = sizeof(double) * size_t(npan) * p * p + sizeof(T) * size_t(pl->n) * p;
     auto launch = [&](auto kernel) {
-      HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+      allow_dynamic_lds(reinterpret_cast<const void*>(kernel));
       hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallOrthThreads), lds, s, int(pl->n), npan, Vb, W,
                          Vout, H, ldh, col0, Rhat, shift_rel, w.flags);
     };
@@ -1767,8 +1778,7 @@ void panel_gemm(expmv_plan_s* pl, int p, const T* V, int npan, const double* C, 
   const int64_t rows_per_wg = ((tiles + nwg - 1) / nwg) * TR;
   const int grid = int((n + rows_per_wg - 1) / rows_per_wg);
   const size_t lds = lds_for(TR);
-  HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_panel_gemm<T, TO>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  allow_dynamic_lds(reinterpret_cast<const void*>(&k_panel_gemm<T, TO>));
   hipLaunchKernelGGL((k_panel_gemm<T, TO>), dim3(grid, nchunks), dim3(kThreads), lds, pl->stream, n,
                      p, V, npan, C, ldc, out, chunk_stride, ldo, accumulate, TR, rows_per_wg);
 }
@@ -2016,8 +2026,7 @@ void proj_solve(hipStream_t s, int ns, int d, int p, int precond, const double* 
                 const double* tau_re, const double* tau_im, const cplx* G, cplx* Ascr, cplx* Zs,
                 double* Cr, int ldc, cplx* S, double* rho, int* singular) {
   if (const size_t lds = proj_small_lds(d, p); d <= 96 && lds <= kProjSmallLds) {
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_proj_solve_small),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    allow_dynamic_lds(reinterpret_cast<const void*>(&k_proj_solve_small));
     hipLaunchKernelGGL(k_proj_solve_small, dim3(ns), dim3(kProjSmallThreads), lds, s, d, p, precond,
                        H, ldh, tau_re, tau_im, G, Cr, ldc, S, rho, singular);
     return;

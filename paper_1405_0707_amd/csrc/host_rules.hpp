@@ -2,6 +2,10 @@
 // that it can be checked on a CPU.
 #pragma once
 
+#include <mutex>
+#include <set>
+#include <utility>
+
 #ifdef __HIPCC__
 #define EXPMV_HOST_DEVICE __host__ __device__
 #else
@@ -15,6 +19,21 @@ namespace expmv {
 // ends within `most` of it.
 EXPMV_HOST_DEVICE inline int chunk_end(int b, int e, int most) {
   return e - b > most ? b + most : e;
+}
+
+// Calls set() on the first use of `kernel` on `device` in the process, and
+// returns only after a set() that did not throw.  For kernel attributes, which
+// belong to the function and not to a plan: they are set once, to a value that
+// serves every launch, so that plans on several threads cannot lower each
+// other's.  One entry is kept per kernel and device.
+template <typename Set>
+void once_per_kernel(const void* kernel, int device, Set&& set) {
+  static std::mutex mutex;
+  static std::set<std::pair<const void*, int>> done;
+  std::lock_guard<std::mutex> lock(mutex);
+  if (done.count({kernel, device})) return;
+  set();
+  done.insert({kernel, device});
 }
 
 }  // namespace expmv

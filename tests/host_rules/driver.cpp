@@ -1,9 +1,13 @@
 // Checks of csrc/host_rules.hpp, built with g++ under UndefinedBehaviorSanitizer
 // by tests/test_host_rules.py.
+#include <atomic>
 #include <climits>
 #include <cstdint>
 #include <cstdio>
 #include <initializer_list>
+#include <stdexcept>
+#include <thread>
+#include <vector>
 
 #include "host_rules.hpp"
 
@@ -37,6 +41,43 @@ int main() {
     }
   check(ordinary, "chunks of ordinary runs");
   check(at_the_limit, "chunks of runs that end near INT32_MAX");
+
+  // several threads, each using every kernel on two devices: one set() per
+  // kernel and device, finished before any thread goes on to its launch
+  const int kernels = 6, threads = 8;
+  static char fn[kernels];
+  std::atomic<int> sets[2][kernels] = {};
+  std::atomic<bool> early{false};
+  std::vector<std::thread> pool;
+  for (int t = 0; t < threads; ++t)
+    pool.emplace_back([&, t]() {
+      for (int i = 0; i < 2000; ++i) {
+        const int k = (i + t) % kernels, d = (i / kernels) % 2;
+        once_per_kernel(&fn[k], d, [&]() {
+          std::this_thread::yield();
+          ++sets[d][k];
+        });
+        if (sets[d][k].load() != 1) early = true;
+      }
+    });
+  for (auto& th : pool) th.join();
+  bool once = true;
+  for (auto& dev : sets)
+    for (auto& s : dev) once = once && s.load() == 1;
+  check(once && !early.load(), "attributes set once per kernel and device, before use");
+
+  // a set() that fails is tried again
+  static char other;
+  int calls = 0;
+  for (int i = 0; i < 3; ++i) {
+    try {
+      once_per_kernel(&other, 0, [&]() {
+        if (++calls == 1) throw std::runtime_error("refused");
+      });
+    } catch (const std::runtime_error&) {
+    }
+  }
+  check(calls == 2, "a failed setting is repeated, a successful one is not");
   if (!fails) std::printf("ALL OK\n");
   return fails != 0;
 }
