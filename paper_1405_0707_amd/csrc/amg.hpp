@@ -21,6 +21,14 @@
 
 namespace expmv {
 
+// Workgroup size of the finest-level passes that keep the inner solver's grid:
+// 1024 with one column per lane, whose loads in flight 512 threads halve (FP32
+// smoothing step at 70^3, p = 31: 221 against 134 us; prolongation 130 against
+// 86; at 10^6 rows, p = 5, 150 against 90).  A single FP64 column is no faster
+// with 1024.
+template <typename T, int PPL, int VW>
+constexpr int amg_fine_threads() { return VW == 1 && (PPL >= 4 || sizeof(T) == 4) ? 1024 : kCgThreads; }
+
 enum : int {
   kAmgX0 = 1,      // x (and the previous d) = s0 D^{-1} b, not stored
   kAmgResid = 2,   // out = b - A x instead of a smoothing step
@@ -284,13 +292,13 @@ k_amg_step(int k, const KrylovCtl* ctl, int n, int p, int G, const int32_t* __re
 #pragma unroll
     for (int q = 0; q < VW; ++q) rz[q] += bi[q] * o[q];
   }
-  if constexpr (NT == kCgThreads) {
+  if constexpr (SEG) {
     if (mode & kAmgRz) {
-      __shared__ double red[kCgThreads];
+      __shared__ double red[NT];
       // column c0 + q of this lane into part[wg][0][c0 + q] (layout of PP = PPL VW)
 #pragma unroll
       for (int q = 0; q < VW; ++q) {
-        wave_col_reduce<PPL, kCgThreads>(rz[q], red);
+        wave_col_reduce<PPL, NT>(rz[q], red);
         if (threadIdx.x < PPL)
           part[size_t(blockIdx.x) * (2 * PPL * VW) + VW * threadIdx.x + q] = red[threadIdx.x];
         __syncthreads();

@@ -370,55 +370,67 @@ constexpr bool kWide8 = sizeof(T) == 4 && PP >= 16;
     }                                                                        \
   } while (0)
 
+// Workgroup size of the inner solver's vector updates (cg_update_threads): NT_
+#define NT_DISPATCH(nt, ...)                              \
+  do {                                                    \
+    if (VW_ == 1 && (nt) != kCgThreads) {                 \
+      constexpr int NT_ = VW_ == 1 ? 1024 : kCgThreads;   \
+      __VA_ARGS__;                                        \
+    } else {                                              \
+      constexpr int NT_ = kCgThreads;                     \
+      __VA_ARGS__;                                        \
+    }                                                     \
+  } while (0)
+
 // Lane width of the BiCGStab vector updates (k_bcg_u1/u2/u3): four FP64
 // columns per lane (two 16-byte accesses) for blocks of 16 or more columns
 // with p a multiple of 4, else as the SpMMs.  On the 128^3 workload u1 and u3
 // took 0.247 / 0.472 ms at two columns and 0.228 / 0.450 ms at four, while
 // the SpMMs lost at four (0.309 against 0.293 ms).
-#define UPD_DISPATCH(T, PP, p, ...)                                          \
+#define UPD_DISPATCH(T, PP, p, nt, ...)                                      \
   do {                                                                       \
     if constexpr (PP >= 16 && sizeof(T) == 8) {                              \
       if ((p) % 4 == 0) {                                                    \
         constexpr int PPL_ = PP / 4, VW_ = 4;                                \
-        __VA_ARGS__;                                                         \
+        NT_DISPATCH(nt, __VA_ARGS__);                                        \
         break;                                                               \
       }                                                                      \
     }                                                                        \
-    SPMM_DISPATCH(T, PP, p, __VA_ARGS__);                                    \
+    SPMM_DISPATCH(T, PP, p, NT_DISPATCH(nt, __VA_ARGS__));                   \
   } while (0)
 
 // CG kernels (working type T): PPL_ lanes per row with VW_ adjacent columns
 // each, PPL_ VW_ = PP: VW_ = 8 for FP32 blocks of 16 or more columns with p a
 // multiple of 8 (kWide8), else 4 when p is a multiple of 4 and the block is
 // FP32 or at least 16 wide (kWide4), else 2 for even p
-#define CG_CASE(PPV, p, ...)                                                \
+#define CG_CASE(PPV, p, nt, ...)                                            \
   case PPV:                                                                 \
     if constexpr (kWide8<T, PPV>) {                                         \
       if ((p) % 8 == 0) {                                                   \
         constexpr int PPL_ = PPV / 8, VW_ = 8;                              \
-        __VA_ARGS__;                                                        \
+        NT_DISPATCH(nt, __VA_ARGS__);                                       \
         break;                                                              \
       }                                                                     \
     }                                                                       \
     if constexpr (kWide4<T, PPV>) {                                         \
       if ((p) % 4 == 0) {                                                   \
         constexpr int PPL_ = PPV / 4, VW_ = 4;                              \
-        __VA_ARGS__;                                                        \
+        NT_DISPATCH(nt, __VA_ARGS__);                                       \
         break;                                                              \
       }                                                                     \
     }                                                                       \
     if (PPV >= 2 && (p) % 2 == 0) {                                         \
       constexpr int PPL_ = (PPV >= 2 ? PPV / 2 : 1), VW_ = (PPV >= 2 ? 2 : 1); \
-      __VA_ARGS__;                                                          \
+      NT_DISPATCH(nt, __VA_ARGS__);                                         \
     } else {                                                                \
       constexpr int PPL_ = PPV, VW_ = 1;                                    \
-      __VA_ARGS__;                                                          \
+      NT_DISPATCH(nt, __VA_ARGS__);                                         \
     }                                                                       \
     break;
-#define DISPATCH_CG(PP, p, ...)                                                       \
+#define DISPATCH_CG(PP, p, nt, ...)                                                   \
   switch (PP) {                                                                       \
-    CG_CASE(1, p, __VA_ARGS__) CG_CASE(2, p, __VA_ARGS__) CG_CASE(4, p, __VA_ARGS__)  \
-    CG_CASE(8, p, __VA_ARGS__) CG_CASE(16, p, __VA_ARGS__) CG_CASE(32, p, __VA_ARGS__) \
+    CG_CASE(1, p, nt, __VA_ARGS__) CG_CASE(2, p, nt, __VA_ARGS__) CG_CASE(4, p, nt, __VA_ARGS__)  \
+    CG_CASE(8, p, nt, __VA_ARGS__) CG_CASE(16, p, nt, __VA_ARGS__) CG_CASE(32, p, nt, __VA_ARGS__) \
   }
 
 // Lay out the call's workspace in `work` (nullptr: size only) and return its
@@ -610,7 +622,7 @@ void toeplitz_apply(expmv_plan_s* pl, const T* X, int64_t ldx, T* Y, int64_t ldy
 template <typename T>
 void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, double scale);
 
-int cg_grid(int64_t n, int PP, int p);
+int grid_lanes(int64_t n, int lanes, int nt);
 
 // Whether the SpMMs stage the operator's entries through LDS (spmm_rows).
 int staged_rows(const expmv_plan_s* pl) { return pl->nnz <= 8 * pl->n ? 1 : 0; }
@@ -624,8 +636,9 @@ void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double sc
   }
   Csr<T> A = csr_of<T>(pl, transpose);
   const int PP = pow2_lanes(p);
+  const int grid = grid_lanes(pl->n, p % 2 == 0 ? PP / 2 : PP, kCgThreads);
   DISPATCH_PP(PP, SPMM_DISPATCH(T, P_, p,
-                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(cg_grid(pl->n, PP, p)),
+                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(grid),
                                                    dim3(kCgThreads), 0, pl->stream, int(pl->n), p,
                                                    A.rowptr, A.colind, A.val, staged_rows(pl), X, Y,
                                                    scale)));
@@ -678,17 +691,39 @@ struct InnerResult {
   int hit_cap;
 };
 
-// Workgroups (of kCgThreads) that take n rows of `lanes` lanes in one pass, at
+// Workgroups (of nt threads) that take n rows of `lanes` lanes in one pass, at
 // most kCgGrid, a multiple of 8 from 8 on (xcd_rows, StreamRows).
-int grid_lanes(int64_t n, int lanes) {
+int grid_lanes(int64_t n, int lanes, int nt) {
   const int64_t g = std::max<int64_t>(
-      1, std::min<int64_t>(kCgGrid, (n * lanes + kCgThreads - 1) / kCgThreads));
+      1, std::min<int64_t>(kCgGrid, (n * lanes + nt - 1) / nt));
   return int(g < 8 ? g : (g + 7) / 8 * 8);
 }
 
 // Grid of the inner-solver kernels for p columns (PP = p rounded up to a power
-// of two): two columns per lane when p is even.
-int cg_grid(int64_t n, int PP, int p) { return grid_lanes(n, p % 2 == 0 ? PP / 2 : PP); }
+// of two), two columns per lane when p is even: the rows in one pass.  Every
+// workgroup of an update sums the partials of all of them (16 PP bytes each), so
+// g workgroups read 16 PP g^2 bytes from the caches.  With one column per lane
+// the rows take twice the workgroups; above 20 MB they take two passes instead:
+// n = 8,000, p = 31 read 260 MB, u3 / u1 / u2 took 32 / 31 / 18 us, the inverse
+// 6.6 ms, now 3.1; 181^2, p = 5 (33 MB) 16.1 ms, now 12.3.  255^2, p = 3 (17 MB) is
+// faster in one pass (a time sweep 41.1 against 42.5 ms).
+int cg_grid(int64_t n, int PP, int p) {
+  if (p % 2 == 0) return grid_lanes(n, PP / 2, kCgThreads);
+  const int g = grid_lanes(n, PP, kCgThreads);
+  return p == 1 || 16.0 * PP * g * g <= 20e6 ? g : grid_lanes(n, PP, 2 * kCgThreads);
+}
+
+// Workgroup size of the vector updates.  Odd p, one column per lane: 1024
+// threads from 10 passes of 512 workgroups of 512 on (4 for p = 3), as fewer
+// loads are in flight per thread; below, the opening reduction and the barriers
+// of the larger workgroups cost more.  Jacobi-CG with 512 and 1024 threads:
+// 300^2 p = 5 (3 passes) 19.3 and 22.6 ms, p = 9 (6) 35.0 and 38.3, p = 17 (11)
+// 62.5 and 58.9; 500^2 p = 5 (8) 56.9 and 59.4, p = 9 (16) 98.3 and 96.7, p = 17
+// (31) 182 and 164, p = 3 (4) 32.1 and 31.0; p = 1 no gain.
+int cg_update_threads(int64_t n, int PP, int p) {
+  if (p % 2 == 0 || p == 1) return kCgThreads;
+  return n * PP > (int64_t(PP <= 4 ? 4 : 10) << 18) ? 1024 : kCgThreads;
+}
 
 double inner_tol_of(expmv_plan_s* pl) {
   const double base = pl->opts.inner_tol > 0.0 ? pl->opts.inner_tol : (pl->mixed ? 1e-6 : 1e-12);
@@ -762,7 +797,7 @@ void amg_level(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out, in
 template <typename T, int PPL, int VW>
 void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out, int k,
                   const KrylovCtl* ctl, double* part_rz) {
-  constexpr int PP = PPL * VW;
+  constexpr int PP = PPL * VW, NT = amg_fine_threads<T, PPL, VW>();
   AmgDevLevel& L = *H.lv[l];
   hipStream_t s = pl->stream;
   const int n = int(L.n);
@@ -854,8 +889,8 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
     if (mode & kAmgWriteD) bytes += blk;
     const KtEv e = kt_take(pl, c_smooth, bytes);
     if (fine)
-      hipExtLaunchKernelGGL((k_amg_step<T, PPL, VW, kCgThreads, true>), dim3(gfine),
-                            dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k, ctl, n, p, GA, L.arp, L.aci,
+      hipExtLaunchKernelGGL((k_amg_step<T, PPL, VW, NT, true>), dim3(gfine),
+                            dim3(NT), 0, s, e.e0, e.e1, 0, k, ctl, n, p, GA, L.arp, L.aci,
                             lv.a, dinv, b, x, d, o, L.ad[0], cd, ad, mode, part);
     else
       hipExtLaunchKernelGGL((k_amg_step<T, PPL, VW, kThreads, false>), dim3(gcoarse_a),
@@ -888,8 +923,8 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
     const KtEv e = kt_take(pl, c_prol, csr(n, L.nnz_a) + es * n + blk + csr(n, L.nnz_p) + cblk +
                                            blk);
     const int G = std::max(GA, GP);
-    hipExtLaunchKernelGGL((k_amg_affine_pair<T, PPL, VW, kCgThreads, true>),
-                          dim3(grid_lanes(n, PPL * G)), dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k,
+    hipExtLaunchKernelGGL((k_amg_affine_pair<T, PPL, VW, NT, true>),
+                          dim3(grid_lanes(n, PPL * G, NT)), dim3(NT), 0, s, e.e0, e.e1, 0, k,
                           ctl, n, p, G, L.arp, L.aci, lv.a, dinv, b, L.Prp.p, L.Pci.p, lv.p, xc, L.alpha, L.beta,
                           x);
   } else {
@@ -922,8 +957,8 @@ void amg_level_vw(expmv_plan_s* pl, AmgDev& H, int l, int p, const T* b, T* out,
     const double pb = csr(n, L.nnz_p) + cblk + blk + (implicit ? es * n + blk : blk);
     const KtEv e = kt_take(pl, c_prol, pb);
     if (fine)
-      hipExtLaunchKernelGGL((k_amg_prolong<T, PPL, VW, kCgThreads, true>), dim3(gfine),
-                            dim3(kCgThreads), 0, s, e.e0, e.e1, 0, k, ctl, n, p, GP, L.Prp.p,
+      hipExtLaunchKernelGGL((k_amg_prolong<T, PPL, VW, NT, true>), dim3(gfine),
+                            dim3(NT), 0, s, e.e0, e.e1, 0, k, ctl, n, p, GP, L.Prp.p,
                             L.Pci.p, lv.p, xc, dinv, b, L.ad[0], pmode, x);
     else
       hipExtLaunchKernelGGL((k_amg_prolong<T, PPL, VW, kThreads, false>), dim3(gcoarse_p),
@@ -1054,6 +1089,7 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
   const int64_t n = pl->n;
   const int PP = pow2_lanes(p);
   const int grid = cg_grid(n, PP, p);
+  const int nt = cg_update_threads(n, PP, p);
   const double tol = inner_tol_of(pl);
   const double tol2 = tol * tol;
   const int maxit = pl->opts.inner_maxit;
@@ -1073,7 +1109,8 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
     r32 = w.kr32;
     z32 = w.kz32;
   }
-  DISPATCH_CG(PP, p, hipLaunchKernelGGL((k_cg_init<T, T, PPL_, VW_>), dim3(grid), dim3(kCgThreads), 0, s,
+  DISPATCH_CG(PP, p, nt, hipLaunchKernelGGL((k_cg_init<T, T, PPL_, VW_, NT_>), dim3(grid),
+                                            dim3(NT_), 0, s,
                                      int(n), p, sign, src, A.dinv, out, r, P[0], w.ctl,
                                      w.part_rr, r32));
   auto vcycle = [&](int k) {
@@ -1100,13 +1137,13 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
       kt.sampling = pl->opts.profile > 0 && ((k + 1) % pl->opts.profile) == 0;
       const KtEv ec = kt_take(pl, EXPMV_KT_CG_DIR, by_c);
       if (v32) {
-        DISPATCH_CG(PP, p, hipExtLaunchKernelGGL((k_cg_c<T, float, PPL_, VW_>), dim3(grid),
-                                                 dim3(kCgThreads), 0, s, ec.e0, ec.e1, 0, k,
+        DISPATCH_CG(PP, p, nt, hipExtLaunchKernelGGL((k_cg_c<T, float, PPL_, VW_, NT_>), dim3(grid),
+                                                 dim3(NT_), 0, s, ec.e0, ec.e1, 0, k,
                                                  int(n), p, A.dinv, r, z32, pold, pnew, out,
                                                  w.cgst, w.ctl, w.part_rr, tol2, maxit));
       } else {
-        DISPATCH_CG(PP, p, hipExtLaunchKernelGGL((k_cg_c<T, T, PPL_, VW_>), dim3(grid),
-                                                 dim3(kCgThreads), 0, s, ec.e0, ec.e1, 0, k,
+        DISPATCH_CG(PP, p, nt, hipExtLaunchKernelGGL((k_cg_c<T, T, PPL_, VW_, NT_>), dim3(grid),
+                                                 dim3(NT_), 0, s, ec.e0, ec.e1, 0, k,
                                                  int(n), p, A.dinv, r, z, pold, pnew, out,
                                                  w.cgst, w.ctl, w.part_rr, tol2, maxit));
       }
@@ -1117,8 +1154,8 @@ InnerResult inner_cg(expmv_plan_s* pl, const T* src, double sign, T* out, int p)
                                                           k, int(n), p, A.rowptr, A.colind, A.val,
                                                           staged_rows(pl), pnew, q, w.ctl, w.part_sig)));
       const KtEv eb = kt_take(pl, EXPMV_KT_CG_RESID, by_b);
-      DISPATCH_CG(PP, p, hipExtLaunchKernelGGL((k_cg_b<T, PPL_, VW_>), dim3(grid),
-                                               dim3(kCgThreads), 0, s, eb.e0, eb.e1, 0, k, int(n),
+      DISPATCH_CG(PP, p, nt, hipExtLaunchKernelGGL((k_cg_b<T, PPL_, VW_, NT_>), dim3(grid),
+                                               dim3(NT_), 0, s, eb.e0, eb.e1, 0, k, int(n),
                                                p, A.dinv, r, q, w.cgst, w.ctl, w.part_sig,
                                                w.part_rr, amg ? 0 : 1, r32));
       if (amg) vcycle(k);
@@ -1151,6 +1188,7 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
   const int64_t n = pl->n;
   const int PP = pow2_lanes(p);
   const int grid = cg_grid(n, PP, p);
+  const int nt = cg_update_threads(n, PP, p);
   const double tol = inner_tol_of(pl);
   const double tol2 = tol * tol;
   const int maxit = pl->opts.inner_maxit;
@@ -1165,8 +1203,10 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
   T* ph = H ? reinterpret_cast<T*>(w.kph) : nullptr;   // M^{-1} p
   T* sh = H ? reinterpret_cast<T*>(w.ksh) : nullptr;   // M^{-1} s
   const T* dscale = H ? nullptr : A.dinv;
-  DISPATCH_PP(PP, hipLaunchKernelGGL((k_bcg_init<T, T, P_>), dim3(grid), dim3(kCgThreads), 0, s,
-                                     int(n), p, sign, src, out, r, rh, w.ctl, w.part_rr));
+  DISPATCH_PP(PP, UPD_DISPATCH(T, P_, p, nt,
+                                hipLaunchKernelGGL((k_bcg_init<T, T, P_, NT_>),
+                                                   dim3(grid), dim3(NT_), 0, s, int(n),
+                                                   p, sign, src, out, r, rh, w.ctl, w.part_rr)));
   // timed bytes per launch: each SpMM reads K (CSR), its input (gathered)
   // and the vector its partials pair with, and writes its output (+ D^{-1}
   // for Jacobi); u1 reads r, p, v and writes p (reads r only at i = 0);
@@ -1183,25 +1223,25 @@ InnerResult inner_bicgstab(expmv_plan_s* pl, int transpose, const T* src, double
       kt.sampling = pl->opts.profile > 0 && ((i + 1) % pl->opts.profile) == 0;
       DISPATCH_PP(PP, {
         const KtEv e1 = kt_take(pl, EXPMV_KT_BCG_U1, (i == 0 ? 2 : 4) * blk);
-        UPD_DISPATCH(T, P_, p,
-                      hipExtLaunchKernelGGL((k_bcg_u1<T, PPL_, VW_>), dim3(grid),
-                                            dim3(kCgThreads), 0, s, e1.e0, e1.e1, 0, i, int(n),
+        UPD_DISPATCH(T, P_, p, nt,
+                      hipExtLaunchKernelGGL((k_bcg_u1<T, PPL_, VW_, NT_>), dim3(grid),
+                                            dim3(NT_), 0, s, e1.e0, e1.e1, 0, i, int(n),
                                             p, r, pv, v, w.bcgst, w.ctl, w.part_rr, tol2, maxit));
         if (H) amg_vcycle<T>(pl, *H, p, pv, ph, i, w.ctl, nullptr);
         bcg_spmm<T, P_, 1>(s, kt_take(pl, EXPMV_KT_BCG_SPMM1, by_s), grid, i, int(n), p, A.rowptr,
                            A.colind, A.val, staged_rows(pl), dscale, H ? ph : pv, rh, v, w.ctl, w.part_sig);
         const KtEv e2 = kt_take(pl, EXPMV_KT_BCG_U2, 3 * blk);
-        UPD_DISPATCH(T, P_, p,
-                      hipExtLaunchKernelGGL((k_bcg_u2<T, PPL_, VW_>), dim3(grid),
-                                            dim3(kCgThreads), 0, s, e2.e0, e2.e1, 0, i, int(n),
+        UPD_DISPATCH(T, P_, p, nt,
+                      hipExtLaunchKernelGGL((k_bcg_u2<T, PPL_, VW_, NT_>), dim3(grid),
+                                            dim3(NT_), 0, s, e2.e0, e2.e1, 0, i, int(n),
                                             p, r, v, sv, w.bcgst, w.ctl, w.part_sig));
         if (H) amg_vcycle<T>(pl, *H, p, sv, sh, i, w.ctl, nullptr);
         bcg_spmm<T, P_, 2>(s, kt_take(pl, EXPMV_KT_BCG_SPMM2, by_s), grid, i, int(n), p, A.rowptr,
                            A.colind, A.val, staged_rows(pl), dscale, H ? sh : sv, sv, tv, w.ctl, w.part_sig);
         const KtEv e3 = kt_take(pl, EXPMV_KT_BCG_U3, by_u3);
-        UPD_DISPATCH(T, P_, p,
-                      hipExtLaunchKernelGGL((k_bcg_u3<T, PPL_, VW_>), dim3(grid),
-                                            dim3(kCgThreads), 0, s, e3.e0, e3.e1, 0, i, int(n),
+        UPD_DISPATCH(T, P_, p, nt,
+                      hipExtLaunchKernelGGL((k_bcg_u3<T, PPL_, VW_, NT_>), dim3(grid),
+                                            dim3(NT_), 0, s, e3.e0, e3.e1, 0, i, int(n),
                                             p, A.dinv, pv, sv, tv, rh, ph, sh, out, r, w.bcgst,
                                             w.ctl, w.part_sig, w.part_rr));
       });

@@ -4,9 +4,10 @@
 // workgroups and a grid-stride loop over rows; a group of PP lanes (PP = p
 // rounded up to a power of two, PP | 64) owns one row, so every row's p
 // values are one contiguous, coalesced segment.  The inner-solver kernels
-// (kCgThreads-thread workgroups) give each lane VW = 2 adjacent columns when p is
-// even, so PPL = PP / 2 lanes own a row and loads are 16 bytes wide; for odd
-// p, VW = 1 and PPL = PP.  Reductions are
+// (kCgThreads-thread workgroups) give each lane VW adjacent columns, so that
+// PPL = PP / VW lanes own a row: two for even p (16-byte loads in FP64), four or
+// eight for the wider blocks of the dispatch macros in expmv.hip, one for odd p
+// (whose vector updates on long blocks run 1024 threads).  Reductions are
 // deterministic: per-workgroup partial sums in a fixed tree order, then a
 // fixed-order sum over workgroups (no floating-point atomics).
 #pragma once
@@ -25,7 +26,9 @@ constexpr int kThreads = 256;
 // each pays its opening reduction once and one computes while the other waits
 // at a barrier.  With 1024 threads (one per CU, two generations) the SpMM of
 // the 128^3 operator at p = 16 took 281 us against 243, the CG's direction
-// update at 64^3, p = 8, 25.6 against 21.0 us.
+// update at 64^3, p = 8, 25.6 against 21.0 us.  One column per lane (odd p) has
+// too few bytes in flight that way where a vector update or a gather of the
+// finest level makes many passes: cg_update_threads, amg_fine_threads.
 constexpr int kCgThreads = 512;
 constexpr int kCgWaves = 4;
 constexpr int kNShift = 7;   // conjugate-pair poles of the degree-14 CF form
@@ -181,11 +184,11 @@ struct CgState {
 
 // Sum NV x PP per-workgroup partials (layout [wg][v][c]) in a fixed order;
 // every thread of the workgroup ends with out[v * PP + c] in LDS.
-template <int PP, int NV>
+template <int PP, int NV, int NT>
 __device__ inline void reduce_parts(const double* __restrict__ part, int nwg, double* red,
                                     double* out) {
   constexpr int slots = PP * NV;
-  constexpr int lanes = (kCgThreads / slots) > 64 ? 64 : kCgThreads / slots;
+  constexpr int lanes = (NT / slots) > 64 ? 64 : NT / slots;
   const int tid = threadIdx.x;
   const int sidx = tid / lanes, l = tid % lanes;
   double v = 0.0;
@@ -221,21 +224,21 @@ __device__ inline void reduce_parts(const double* __restrict__ part, int nwg, do
 }
 
 // per-workgroup column sums of v (PP columns) -> part[wg * stride + off + c]
-template <int PP>
+template <int PP, int NT>
 __device__ inline void write_col_partial(double v, double* red, double* part, int stride, int off) {
-  wave_col_reduce<PP, kCgThreads>(v, red);
+  wave_col_reduce<PP, NT>(v, red);
   if (threadIdx.x < PP) part[size_t(blockIdx.x) * stride + off + threadIdx.x] = red[threadIdx.x];
   __syncthreads();
 }
 
 // The same layout when each lane holds VW adjacent columns: lane l's value q
 // is column VW l + q of the PPL VW columns.
-template <int PPL, int VW>
+template <int PPL, int VW, int NT>
 __device__ inline void write_col_partial_vw(const double (&v)[VW], double* red, double* part,
                                             int stride, int off) {
 #pragma unroll
   for (int q = 0; q < VW; ++q) {
-    wave_col_reduce<PPL, kCgThreads>(v[q], red);
+    wave_col_reduce<PPL, NT>(v[q], red);
     if (threadIdx.x < PPL)
       part[size_t(blockIdx.x) * stride + off + VW * threadIdx.x + q] = red[threadIdx.x];
     __syncthreads();
@@ -556,36 +559,36 @@ __device__ inline void spmm_rows(int staged, int64_t n, const int32_t* __restric
                                  Body&& body) {
   int64_t seg0, seg1;
   xcd_rows(n, seg0, seg1);
-  constexpr int S = spmm_stage<PPL>();
+  constexpr int S = spmm_stage<PPL>(), NT = kCgThreads;
   if constexpr (S > 0) {
-    __shared__ double sv[2 * S * kCgThreads];
-    __shared__ int32_t sj[2 * S * kCgThreads];
+    __shared__ double sv[2 * S * NT];
+    __shared__ int32_t sj[2 * S * NT];
     if (staged) {
-      csr_rows_staged<S, spmm_unroll<T, VW>(), PPL, VW, kCgThreads>(
+      csr_rows_staged<S, spmm_unroll<T, VW>(), PPL, VW, NT>(
           rowptr, colind, val, x, dinv, ld, c0, active, seg0, seg1, sj, sv, body);
       return;
     }
   }
   csr_rows_pipelined<spmm_unroll<T, VW>(), VW>(rowptr, colind, val, x, dinv, ld, c0, active,
-                                               seg0 + threadIdx.x / PPL, kCgThreads / PPL, seg1,
+                                               seg0 + threadIdx.x / PPL, NT / PPL, seg1,
                                                body);
 }
 
 // The CG kernels take VW adjacent columns per lane (VW = 2 for even p) and
 // PPL = PP / VW lanes per row; per-column scalars and partials keep the layout
 // of PP columns.
-template <typename T, typename TS, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, typename TS, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __restrict__ dinv,
           T* __restrict__ x, T* __restrict__ r, T* __restrict__ pold,
           KrylovCtl* ctl, double* __restrict__ part_rr, float* __restrict__ r32) {
   constexpr int PP = PPL * VW;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   const int c0 = VW * (threadIdx.x % PPL);
   double rz[VW], bb[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) rz[q] = bb[q] = 0.0;
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t i = row * p + c0;
@@ -609,8 +612,8 @@ k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __rest
       st_vw<VW>(pold + i, zero);
     }
   }
-  write_col_partial_vw<PPL, VW>(rz, red, part_rr, 2 * PP, 0);
-  write_col_partial_vw<PPL, VW>(bb, red, part_rr, 2 * PP, PP);
+  write_col_partial_vw<PPL, VW, NT>(rz, red, part_rr, 2 * PP, 0);
+  write_col_partial_vw<PPL, VW, NT>(bb, red, part_rr, 2 * PP, PP);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->done = -1;
     ctl->iters_max = 0;
@@ -621,22 +624,22 @@ k_cg_init(int n, int p, double sign, const TS* __restrict__ src, const T* __rest
 
 // z: the preconditioned residual (TZ = float for an FP32 V-cycle), or NULL
 // for Jacobi (D^{-1} r formed here)
-template <typename T, typename TZ, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, typename TZ, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
        const TZ* __restrict__ z, const T* __restrict__ pold, T* __restrict__ pnew,
        T* __restrict__ x, CgState* st, KrylovCtl* ctl, const double* __restrict__ part_rr,
        double tol2, int maxit) {
   constexpr int PP = PPL * VW;
   if (finished_before(ctl, k)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   __shared__ double tot[2 * PP];
   __shared__ double s_beta[PP], s_aprev[PP];
   __shared__ int s_any;
   // the operands of this thread's first row are loaded before the scalar
   // reduction, so their latency overlaps it (they are final at kernel start)
   const int c0 = VW * (threadIdx.x % PPL);
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   const int64_t row0 = rows.r;
   const bool pre = row0 < rows.end && c0 < p;
   T po0[VW], xv0[VW], zr0[VW];
@@ -653,7 +656,7 @@ k_cg_c(int k, int n, int p, const T* __restrict__ dinv, const T* __restrict__ r,
       ld_vw<VW>(r + i, zr0);
     }
   }
-  reduce_parts<PP, 2>(part_rr, gridDim.x, red, tot);   // tot[c] = rho_k, tot[PP + c] = |r_k|^2
+  reduce_parts<PP, 2, NT>(part_rr, gridDim.x, red, tot);   // tot[c] = rho_k, tot[PP + c] = |r_k|^2
   if (threadIdx.x < 64) {
     // one lane per column (PP <= 64), the control word from the wavefront's
     // reductions: the scalar loads of all columns are in flight together
@@ -769,9 +772,9 @@ __global__ void __launch_bounds__(kCgThreads, kCgWaves)
 k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
        const double* __restrict__ val, int staged, const T* __restrict__ pk, T* __restrict__ q,
        const KrylovCtl* ctl, double* __restrict__ part_sig) {
-  constexpr int PP = PPL * VW;
+  constexpr int PP = PPL * VW, NT = kCgThreads;
   if (finished_by(ctl, k)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   const int c0 = VW * (threadIdx.x % PPL);
   double sig[VW];
 #pragma unroll
@@ -790,7 +793,7 @@ k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* _
 #pragma unroll
         for (int u = 0; u < VW; ++u) sig[u] += double(pv[u]) * double(qv[u]);
       });
-  write_col_partial_vw<PPL, VW>(sig, red, part_sig, PP, 0);
+  write_col_partial_vw<PPL, VW, NT>(sig, red, part_sig, PP, 0);
 }
 
 // y = scale K x, in the launch shape of the inner solvers' products
@@ -812,19 +815,19 @@ k_spmm(int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restri
       });
 }
 
-template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const T* __restrict__ q,
        CgState* st, const KrylovCtl* ctl, const double* __restrict__ part_sig,
        double* __restrict__ part_rr, int jacobi, float* __restrict__ r32) {
   constexpr int PP = PPL * VW;
   if (finished_by(ctl, k)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   __shared__ double tot[PP];
   __shared__ double s_alpha[PP];
   // the first row's r and q are loaded before the scalar reduction
   const int c0 = VW * (threadIdx.x % PPL);
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   const int64_t row0 = rows.r;
   const bool pre = row0 < rows.end && c0 < p;
   T rv0[VW], qv0[VW];
@@ -832,7 +835,7 @@ k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const
     ld_vw<VW>(r + row0 * p + c0, rv0);
     ld_vw<VW>(q + row0 * p + c0, qv0);
   }
-  reduce_parts<PP, 1>(part_sig, gridDim.x, red, tot);
+  reduce_parts<PP, 1, NT>(part_sig, gridDim.x, red, tot);
   if (threadIdx.x < PP) {
     const int cc = threadIdx.x;
     double a = 0.0;
@@ -875,8 +878,8 @@ k_cg_b(int k, int n, int p, const T* __restrict__ dinv, T* __restrict__ r, const
       if (r32) st_vw<VW>(r32 + i, r32v);   // input of an FP32 preconditioner
     }
   }
-  if (jacobi) write_col_partial_vw<PPL, VW>(rz, red, part_rr, 2 * PP, 0);
-  write_col_partial_vw<PPL, VW>(rr, red, part_rr, 2 * PP, PP);
+  if (jacobi) write_col_partial_vw<PPL, VW, NT>(rz, red, part_rr, 2 * PP, 0);
+  write_col_partial_vw<PPL, VW, NT>(rr, red, part_rr, 2 * PP, PP);
 }
 
 // ---------------------------------------------------------------------------
@@ -910,14 +913,14 @@ struct BcgState {
   double bnorm2[kMaxP];
 };
 
-template <typename T, typename TS, int PP>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, typename TS, int PP, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_bcg_init(int n, int p, double sign, const TS* __restrict__ src, T* __restrict__ x,
            T* __restrict__ r, T* __restrict__ rhat, KrylovCtl* ctl, double* __restrict__ part_rr) {
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   const int c = threadIdx.x % PP;
   double bb = 0.0;
-  const StreamRows rows(n, kCgThreads / PP, threadIdx.x / PP);
+  const StreamRows rows(n, NT / PP, threadIdx.x / PP);
   for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c < p) {
       const int64_t i = row * p + c;
@@ -928,8 +931,8 @@ k_bcg_init(int n, int p, double sign, const TS* __restrict__ src, T* __restrict_
       bb += double(b) * double(b);
     }
   }
-  write_col_partial<PP>(bb, red, part_rr, 2 * PP, 0);   // (r^, r) = |b|^2 at start
-  write_col_partial<PP>(bb, red, part_rr, 2 * PP, PP);
+  write_col_partial<PP, NT>(bb, red, part_rr, 2 * PP, 0);   // (r^, r) = |b|^2 at start
+  write_col_partial<PP, NT>(bb, red, part_rr, 2 * PP, PP);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->done = -1;
     ctl->iters_max = 0;
@@ -940,17 +943,17 @@ k_bcg_init(int n, int p, double sign, const TS* __restrict__ src, T* __restrict_
 
 // The three BiCGStab updates take VW adjacent columns per lane (PPL = PP / VW
 // lanes per row; VW = 2 for even p: 16-byte FP64 accesses) like the SpMM.
-template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_bcg_u1(int i, int n, int p, const T* __restrict__ r, T* __restrict__ pv, const T* __restrict__ v,
          BcgState* st, KrylovCtl* ctl, const double* __restrict__ part_rr, double tol2, int maxit) {
   constexpr int PP = PPL * VW;
   if (finished_before(ctl, i)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   __shared__ double tot[2 * PP];
   __shared__ double s_beta[PP], s_om[PP];
   __shared__ int s_any;
-  reduce_parts<PP, 2>(part_rr, gridDim.x, red, tot);
+  reduce_parts<PP, 2, NT>(part_rr, gridDim.x, red, tot);
   if (threadIdx.x < 64) {
     // one lane per column, as in k_cg_c
     const int cc = threadIdx.x;
@@ -1019,7 +1022,7 @@ k_bcg_u1(int i, int n, int p, const T* __restrict__ r, T* __restrict__ pv, const
     beta[q] = T(s_beta[(c0 + q) % PP]);
     om[q] = T(s_om[(c0 + q) % PP]);
   }
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
@@ -1047,9 +1050,9 @@ k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* 
         const double* __restrict__ val, int staged, const T* __restrict__ dinv,
         const T* __restrict__ in, const T* __restrict__ a, T* __restrict__ out, const KrylovCtl* ctl,
         double* __restrict__ part) {
-  constexpr int PP = PPL * VW;
+  constexpr int PP = PPL * VW, NT = kCgThreads;
   if (finished_by(ctl, i)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   const int c0 = VW * (threadIdx.x % PPL);
   double d0[VW], d1[VW];
 #pragma unroll
@@ -1072,20 +1075,20 @@ k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* 
           if (NV == 2) d1[q] += o * o;
         }
       });
-  write_col_partial_vw<PPL, VW>(d0, red, part, NV * PP, 0);
-  if (NV == 2) write_col_partial_vw<PPL, VW>(d1, red, part, NV * PP, PP);
+  write_col_partial_vw<PPL, VW, NT>(d0, red, part, NV * PP, 0);
+  if (NV == 2) write_col_partial_vw<PPL, VW, NT>(d1, red, part, NV * PP, PP);
 }
 
-template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, T* __restrict__ sv,
          BcgState* st, const KrylovCtl* ctl, const double* __restrict__ part) {
   constexpr int PP = PPL * VW;
   if (finished_by(ctl, i)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   __shared__ double tot[PP];
   __shared__ double s_a[PP];
-  reduce_parts<PP, 1>(part, gridDim.x, red, tot);
+  reduce_parts<PP, 1, NT>(part, gridDim.x, red, tot);
   if (threadIdx.x < PP) {
     const int cc = threadIdx.x;
     BcgSlot& cur = st->slot[i & 1];
@@ -1099,7 +1102,7 @@ k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, 
   T a[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) a[q] = T(s_a[(c0 + q) % PP]);
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
@@ -1113,8 +1116,8 @@ k_bcg_u2(int i, int n, int p, const T* __restrict__ r, const T* __restrict__ v, 
   }
 }
 
-template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ pv,
          const T* __restrict__ sv, const T* __restrict__ tv, const T* __restrict__ rhat,
          const T* __restrict__ ph, const T* __restrict__ sh, T* __restrict__ x,
@@ -1122,10 +1125,10 @@ k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ 
          double* __restrict__ part_rr) {
   constexpr int PP = PPL * VW;
   if (finished_by(ctl, i)) return;
-  __shared__ double red[kCgThreads];
+  __shared__ double red[NT];
   __shared__ double tot[2 * PP];
   __shared__ double s_a[PP], s_om[PP];
-  reduce_parts<PP, 2>(part, gridDim.x, red, tot);   // tot[c] = (t, s), tot[PP + c] = (t, t)
+  reduce_parts<PP, 2, NT>(part, gridDim.x, red, tot);   // tot[c] = (t, s), tot[PP + c] = (t, t)
   if (threadIdx.x < PP) {
     const int cc = threadIdx.x;
     BcgSlot& cur = st->slot[i & 1];
@@ -1149,7 +1152,7 @@ k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ 
   double rr_hat[VW], rr[VW];
 #pragma unroll
   for (int q = 0; q < VW; ++q) rr_hat[q] = rr[q] = 0.0;
-  const StreamRows rows(n, kCgThreads / PPL, threadIdx.x / PPL);
+  const StreamRows rows(n, NT / PPL, threadIdx.x / PPL);
   for (int64_t row = rows.r; row < rows.end; row += rows.step) {
     if (c0 < p) {
       const int64_t idx = row * p + c0;
@@ -1180,8 +1183,8 @@ k_bcg_u3(int i, int n, int p, const T* __restrict__ dinv, const T* __restrict__ 
       st_vw<VW>(r + idx, rn);
     }
   }
-  write_col_partial_vw<PPL, VW>(rr_hat, red, part_rr, 2 * PP, 0);
-  write_col_partial_vw<PPL, VW>(rr, red, part_rr, 2 * PP, PP);
+  write_col_partial_vw<PPL, VW, NT>(rr_hat, red, part_rr, 2 * PP, 0);
+  write_col_partial_vw<PPL, VW, NT>(rr, red, part_rr, 2 * PP, PP);
 }
 
 // R = V + K W (the residual of M W = V, M = -K) in FP64 from blocks of type
