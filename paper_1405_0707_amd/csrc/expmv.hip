@@ -628,6 +628,14 @@ int grid_lanes(int64_t n, int lanes, int nt);
 int staged_rows(const expmv_plan_s* pl) { return pl->nnz <= 8 * pl->n ? 1 : 0; }
 
 // Y = scale K X (K = -tA, or its transpose) for n x p blocks of type T.
+//
+// One launch in the shape of the inner solvers' products, except for long rows
+// (not staged) of narrow blocks, where two columns per lane leave too few lanes
+// to hide the chain of a row's loads: one column per lane for p = 2, and for p = 4
+// above 16 nonzeros per row (300,000 rows of 27: 77.2 -> 65.4 and 70.7 -> 58.3 us;
+// 10^6 rows of 9, p = 4: 43.9 with two columns, 49.1 with one).  A single column
+// whose rows fit 512 workgroups of 256 threads runs those instead, on more CUs
+// (40,000 rows of 27: 17.5 -> 14.4 us).
 template <typename T>
 void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double scale = 1.0) {
   if (pl->kind == 1) {   // K = t T (or t T^T)
@@ -635,13 +643,19 @@ void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double sc
     return;
   }
   Csr<T> A = csr_of<T>(pl, transpose);
+  const int64_t n = pl->n;
+  const int staged = staged_rows(pl);
+  auto launch = [&](auto kernel, int lanes, int nt) {
+    hipLaunchKernelGGL(kernel, dim3(grid_lanes(n, lanes, nt)), dim3(nt), 0, pl->stream, int(n), p,
+                       A.rowptr, A.colind, A.val, staged, X, Y, scale);
+  };
+  if (!staged && p == 1 && n <= 256 * kCgGrid) return launch(k_spmm<T, 1, 1, 256>, 1, 256);
+  if (!staged && p == 2) return launch(k_spmm<T, 2, 1, kCgThreads>, 2, kCgThreads);
+  if (p == 4 && pl->nnz > 16 * n) return launch(k_spmm<T, 4, 1, kCgThreads>, 4, kCgThreads);
   const int PP = pow2_lanes(p);
-  const int grid = grid_lanes(pl->n, p % 2 == 0 ? PP / 2 : PP, kCgThreads);
   DISPATCH_PP(PP, SPMM_DISPATCH(T, P_, p,
-                                hipLaunchKernelGGL((k_spmm<T, PPL_, VW_>), dim3(grid),
-                                                   dim3(kCgThreads), 0, pl->stream, int(pl->n), p,
-                                                   A.rowptr, A.colind, A.val, staged_rows(pl), X, Y,
-                                                   scale)));
+                                launch(k_spmm<T, PPL_, VW_, kCgThreads>,
+                                       p % 2 == 0 ? PP / 2 : PP, kCgThreads)));
 }
 
 struct KtEv {

@@ -548,10 +548,10 @@ constexpr int spmm_stage() {
   return PPL >= 8 ? 1 : (PPL >= 2 ? 8 / PPL : 0);
 }
 
-// The rows of this workgroup's segment (kCgThreads threads) of y = K x or K D^{-1} x:
+// The rows of this workgroup's segment (NT threads) of y = K x or K D^{-1} x:
 // body(row, sums).  staged: rows of at most 8 nonzeros on average (longer
 // rows would leave most lanes idle in each chunk).
-template <typename T, int PPL, int VW, typename Body>
+template <typename T, int PPL, int VW, int NT, typename Body>
 __device__ inline void spmm_rows(int staged, int64_t n, const int32_t* __restrict__ rowptr,
                                  const int32_t* __restrict__ colind,
                                  const double* __restrict__ val, const T* __restrict__ x,
@@ -559,7 +559,7 @@ __device__ inline void spmm_rows(int staged, int64_t n, const int32_t* __restric
                                  Body&& body) {
   int64_t seg0, seg1;
   xcd_rows(n, seg0, seg1);
-  constexpr int S = spmm_stage<PPL>(), NT = kCgThreads;
+  constexpr int S = spmm_stage<PPL>();
   if constexpr (S > 0) {
     __shared__ double sv[2 * S * NT];
     __shared__ int32_t sj[2 * S * NT];
@@ -780,7 +780,7 @@ k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* _
 #pragma unroll
   for (int u = 0; u < VW; ++u) sig[u] = 0.0;
   const bool active = c0 < p;
-  spmm_rows<T, PPL, VW>(
+  spmm_rows<T, PPL, VW, kCgThreads>(
       staged, n, rowptr, colind, val, pk, static_cast<const T*>(nullptr), p, c0, active,
       [&](int64_t row, const double(&acc)[VW]) {
         if (!active) return;
@@ -797,14 +797,14 @@ k_cg_a(int k, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* _
 }
 
 // y = scale K x, in the launch shape of the inner solvers' products
-template <typename T, int PPL, int VW>
-__global__ void __launch_bounds__(kCgThreads, kCgWaves)
+template <typename T, int PPL, int VW, int NT>
+__global__ void __launch_bounds__(NT, kCgWaves)
 k_spmm(int n, int p, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
        const double* __restrict__ val, int staged, const T* __restrict__ x, T* __restrict__ y,
        double scale) {
   const int c0 = VW * (threadIdx.x % PPL);
   const bool active = c0 < p;
-  spmm_rows<T, PPL, VW>(
+  spmm_rows<T, PPL, VW, NT>(
       staged, n, rowptr, colind, val, x, static_cast<const T*>(nullptr), p, c0, active,
       [&](int64_t row, const double(&acc)[VW]) {
         if (!active) return;
@@ -1058,7 +1058,7 @@ k_bcg_s(int i, int n, int p, const int32_t* __restrict__ rowptr, const int32_t* 
 #pragma unroll
   for (int q = 0; q < VW; ++q) d0[q] = d1[q] = 0.0;
   const bool active = c0 < p;
-  spmm_rows<T, PPL, VW>(
+  spmm_rows<T, PPL, VW, kCgThreads>(
       staged, n, rowptr, colind, val, in, dinv, p, c0, active,
       [&](int64_t row, const double(&accd)[VW]) {
         if (!active) return;
