@@ -344,13 +344,15 @@ constexpr bool kWide8 = sizeof(T) == 4 && PP >= 16;
 
 // Lane width of the inner solvers' SpMMs (k_cg_a, k_bcg_s, k_spmm): 16 bytes
 // of adjacent columns per lane (two FP64 columns for even p, four FP32 ones for
-// p a multiple of 4), so that the eight gathers of a row step (spmm_unroll) fit
-// 128 registers; else two FP32 columns, or one.  Only the columns a lane owns
-// change with the width: the rows of each workgroup, and so the partial sums,
-// do not.
+// p a multiple of 4 from 8 on), so that the eight gathers of a row step
+// (spmm_unroll) fit 128 registers; else two FP32 columns, or one.  Four FP32
+// columns at p = 4 would leave one lane per row, whose entries are not staged:
+// the mixed CG at 300^2 took 17.3 ms with four columns, 15.0 with two, on 40,000
+// rows of 27 nonzeros 577 and 487 us.  Only the columns a lane owns change with
+// the width: the rows of each workgroup, and so the partial sums, do not.
 #define SPMM_DISPATCH(T, PP, p, ...)                                         \
   do {                                                                       \
-    if constexpr (PP >= 4 && sizeof(T) == 4) {                               \
+    if constexpr (PP >= 8 && sizeof(T) == 4) {                               \
       if ((p) % 4 == 0) {                                                    \
         constexpr int PPL_ = PP / 4, VW_ = 4;                                \
         __VA_ARGS__;                                                         \
