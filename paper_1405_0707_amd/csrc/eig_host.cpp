@@ -20,7 +20,7 @@
 
 namespace expmv {
 
-bool sym_eig(int n, const double* Ain, double* w, double* Q) {
+bool sym_eig(int n, const double* Ain, double* w, double* Q, StopToken stop) {
   std::vector<double> A(Ain, Ain + size_t(n) * n);
   auto at = [&](int i, int j) -> double& { return A[size_t(i) * n + j]; };
   auto q = [&](int i, int j) -> double& { return Q[size_t(i) * n + j]; };
@@ -35,6 +35,7 @@ bool sym_eig(int n, const double* Ain, double* w, double* Q) {
     }
   std::vector<double> v(n), pv(n), wv(n);
   for (int k = 0; k + 2 < n; ++k) {
+    stop.check();
     const int m = n - k - 1;  // length of the column part below the diagonal
     double xn = 0.0;
     for (int i = 0; i < m; ++i) xn += at(k + 1 + i, k) * at(k + 1 + i, k);
@@ -80,6 +81,7 @@ bool sym_eig(int n, const double* Ain, double* w, double* Q) {
   int hi = n - 1;
   int guard = 0;
   while (hi > 0 && guard < 60 * n) {
+    stop.check();
     if (std::fabs(b[hi - 1]) <= eps * (std::fabs(a[hi - 1]) + std::fabs(a[hi]))) {
       b[hi - 1] = 0.0;
       --hi;
@@ -194,7 +196,7 @@ void parallel_for(int count, Work&& work) {
 // so that every inner loop runs along a row.  With hf non-null the
 // reflections P_0, P_1, ... of Q = P_0 P_1 ... are kept there (Q itself is
 // only ever applied to a few vectors).
-void hessenberg(int n, std::vector<double>& A, HessForm* hf) {
+void hessenberg(int n, std::vector<double>& A, HessForm* hf, StopToken stop) {
   auto at = [&](int i, int j) -> double& { return A[size_t(i) * n + j]; };
   std::vector<double> v(n), s(n);
   if (hf) {
@@ -203,6 +205,7 @@ void hessenberg(int n, std::vector<double>& A, HessForm* hf) {
     hf->len.assign(n, 0);
   }
   for (int k = 0; k + 2 < n; ++k) {
+    stop.check();
     // rows k+1 .. k+m: up to the last nonzero of column k (the band of a block
     // Hessenberg matrix, as long as it has not filled in)
     int m = n - k - 1;
@@ -279,7 +282,7 @@ void eig2x2(double a, double b, double c, double d, cd& e1, cd& e2) {
 // alone.  Every tenth step without a deflation uses two ad hoc shifts
 // (h_hi,hi + w and h_hi,hi - w/2, w the last two subdiagonal magnitudes)
 // to leave a cycle.
-bool hess_eigenvalues(int n, const std::vector<double>& Hin, std::vector<cd>& ev) {
+bool hess_eigenvalues(int n, const std::vector<double>& Hin, std::vector<cd>& ev, StopToken stop) {
   std::vector<double> H(Hin);
   auto at = [&](int i, int j) -> double& { return H[size_t(i) * n + j]; };
   const double eps = 2.220446049250313e-16;
@@ -287,6 +290,7 @@ bool hess_eigenvalues(int n, const std::vector<double>& Hin, std::vector<cd>& ev
   int hi = n - 1;
   int iter = 0;
   while (hi >= 0) {
+    stop.check();
     if (hi == 0) {
       ev[0] = at(0, 0);
       break;
@@ -466,14 +470,15 @@ struct HessLu {
 };
 }  // namespace
 
-bool general_eigvals(int n, const double* Ain, double* wr, double* wi, HessForm* hf) {
+bool general_eigvals(int n, const double* Ain, double* wr, double* wi, HessForm* hf,
+                     StopToken stop) {
   HessForm local;
   HessForm& f = hf ? *hf : local;
   f.n = n;
   f.H.assign(Ain, Ain + size_t(n) * n);
-  hessenberg(n, f.H, hf);
+  hessenberg(n, f.H, hf, stop);
   std::vector<cd> ev;
-  if (!hess_eigenvalues(n, f.H, ev)) return false;
+  if (!hess_eigenvalues(n, f.H, ev, stop)) return false;
   // make conjugate pairs exact: pair each eigenvalue with Im > tol with the
   // closest conjugate candidate
   double scale = 0.0;
@@ -515,12 +520,13 @@ bool general_eigvals(int n, const double* Ain, double* wr, double* wi, HessForm*
 }
 
 void general_eigvecs(int n, const double* A, const double* wr, const double* wi,
-                     const char* want, double* Vr, double* Vi, const HessForm* hf) {
+                     const char* want, double* Vr, double* Vi, const HessForm* hf,
+                     StopToken stop) {
   HessForm local;
   if (!hf || hf->n != n || hf->refl.size() != size_t(n) * n) {
     local.n = n;
     local.H.assign(A, A + size_t(n) * n);
-    hessenberg(n, local.H, &local);
+    hessenberg(n, local.H, &local, stop);
     hf = &local;
   }
   const std::vector<double>& H = hf->H;
@@ -546,6 +552,7 @@ void general_eigvecs(int n, const double* A, const double* wr, const double* wi,
     for (int r = 0; r < n; ++r) Vr[size_t(r) * n + i] = Vi[size_t(r) * n + i] = 0.0;
   }
   parallel_for(int(wanted.size()), [&](int q) {
+    stop.check();
     const int i = wanted[q];
     HessLu lu;
     lu.factor(n, H, cd(wr[i], wi[i]) + pert);

@@ -9,6 +9,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <complex>
@@ -1850,7 +1851,7 @@ double host_now_ms() {
 
 // Modified Gram-Schmidt (twice) on the columns of P (d x k row-major).
 // Returns the number of independent columns kept (dependent ones dropped).
-int host_orthonormalize_columns(int d, int k, std::vector<double>& P) {
+int host_orthonormalize_columns(int d, int k, std::vector<double>& P, StopToken stop) {
   int kept = 0;
   std::vector<double> cols(size_t(d) * k);   // column by column
   for (int i = 0; i < d; ++i)
@@ -1864,6 +1865,7 @@ int host_orthonormalize_columns(int d, int k, std::vector<double>& P) {
     return (s[0] + s[1]) + (s[2] + s[3]);
   };
   for (int c = 0; c < k; ++c) {
+    stop.check();
     double* v = &cols[size_t(c) * d];
     const double n0 = std::sqrt(dot(v, v));
     for (int pass = 0; pass < 2; ++pass)
@@ -1892,7 +1894,8 @@ struct RitzBasis {
 // The k wanted Ritz vectors of Hd (dlive x dlive): largest |theta| for
 // Algorithm 2 (Remark 4.1), smallest for Algorithm 1; a complex pair is kept
 // whole (real and imaginary parts), so keff may be k + 1.
-RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<double>& Hd, int k) {
+RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<double>& Hd, int k,
+                     StopToken stop) {
   RitzBasis rb;
   std::vector<int> ord(dl);
   std::iota(ord.begin(), ord.end(), 0);
@@ -1900,7 +1903,7 @@ RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<dou
     std::vector<double> wv(dl), Q(size_t(dl) * dl);
     // an unconverged eigen-decomposition would give a restart basis that is
     // not the Ritz basis of Step 5: the solve stops with a breakdown
-    if (!sym_eig(dl, Hd.data(), wv.data(), Q.data())) throw StatusError{EXPMV_EBREAKDOWN};
+    if (!sym_eig(dl, Hd.data(), wv.data(), Q.data(), stop)) throw StatusError{EXPMV_EBREAKDOWN};
     auto key = [&](int a) { return std::fabs(wv[a]); };
     if (precond) std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return key(a) > key(b); });
     else std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return key(a) < key(b); });
@@ -1912,7 +1915,8 @@ RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<dou
   }
   std::vector<double> wr(dl), wi(dl), Vr(size_t(dl) * dl), Vi(size_t(dl) * dl);
   HessForm hf;
-  if (!general_eigvals(dl, Hd.data(), wr.data(), wi.data(), &hf)) throw StatusError{EXPMV_EBREAKDOWN};
+  if (!general_eigvals(dl, Hd.data(), wr.data(), wi.data(), &hf, stop))
+    throw StatusError{EXPMV_EBREAKDOWN};
   auto mag = [&](int a) { return std::hypot(wr[a], wi[a]); };
   if (precond) std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return mag(a) > mag(b); });
   else std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return mag(a) < mag(b); });
@@ -1935,7 +1939,8 @@ RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<dou
         ++chosen;
       }
     }
-    general_eigvecs(dl, Hd.data(), wr.data(), wi.data(), want.data(), Vr.data(), Vi.data(), &hf);
+    general_eigvecs(dl, Hd.data(), wr.data(), wi.data(), want.data(), Vr.data(), Vi.data(), &hf,
+                    stop);
   }
   std::vector<char> taken(dl, 0);
   std::vector<std::vector<double>> cols;
@@ -1966,7 +1971,7 @@ RitzBasis ritz_basis(bool symmetric, bool precond, int dl, const std::vector<dou
   std::vector<double> P(size_t(dl) * kk);
   for (int c = 0; c < kk; ++c)
     for (int i = 0; i < dl; ++i) P[size_t(i) * kk + c] = cols[c][i];
-  const int kept = host_orthonormalize_columns(dl, kk, P);
+  const int kept = host_orthonormalize_columns(dl, kk, P, stop);
   rb.keff = kept;
   rb.Pk.assign(size_t(dl) * kept, 0.0);
   for (int i = 0; i < dl; ++i)
@@ -1986,7 +1991,7 @@ struct RestartCoords {
 };
 
 RestartCoords restart_coordinates(bool symmetric, bool precond, int d, int p, int k, int ldh,
-                                  int keff, int kp, std::vector<double>& Hh) {
+                                  int keff, int kp, std::vector<double>& Hh, StopToken stop) {
   std::vector<int> live;
   for (int i = 0; i < d; ++i)
     if (!(i >= keff && i < kp)) live.push_back(i);
@@ -1994,7 +1999,7 @@ RestartCoords restart_coordinates(bool symmetric, bool precond, int d, int p, in
   std::vector<double> Hd(size_t(dl) * dl);
   for (int i = 0; i < dl; ++i)
     for (int j = 0; j < dl; ++j) Hd[size_t(i) * dl + j] = Hh[size_t(live[i]) * ldh + live[j]];
-  RitzBasis rb = ritz_basis(symmetric, precond, dl, Hd, k);
+  RitzBasis rb = ritz_basis(symmetric, precond, dl, Hd, k, stop);
   RestartCoords rc;
   const int kn = rb.keff;
   const int kpn = (kn + p - 1) / p * p;
@@ -2008,6 +2013,7 @@ RestartCoords restart_coordinates(bool symmetric, bool precond, int d, int p, in
   // H~_new = P_{k+p}^T H~ P_k (both products row by row, inner loops along rows)
   std::vector<double> HP(size_t(d + p) * kn, 0.0);
   for (int i = 0; i < d + p; ++i) {
+    stop.check();
     double* hp = &HP[size_t(i) * kn];
     for (int j = 0; j < d; ++j) {
       const double h = Hh[size_t(i) * ldh + j];
@@ -2018,6 +2024,7 @@ RestartCoords restart_coordinates(bool symmetric, bool precond, int d, int p, in
   }
   std::fill(Hh.begin(), Hh.end(), 0.0);
   for (int i = 0; i < d; ++i) {
+    stop.check();
     const double* pk = &Pk[size_t(i) * kpn];
     const double* hp = &HP[size_t(i) * kn];
     for (int r = 0; r < kn; ++r) {
@@ -2031,6 +2038,14 @@ RestartCoords restart_coordinates(bool symmetric, bool precond, int d, int p, in
     for (int c = 0; c < kn; ++c) Hh[size_t(kpn + r) * ldh + c] = HP[size_t(d + r) * kn + c];
   return rc;
 }
+
+// restart_coordinates on a host thread.  A restart that turns out not to be
+// needed is ended within one step of its loops when this goes out of scope.
+struct RestartTask {
+  std::atomic<bool> stop{false};
+  std::future<RestartCoords> coords;   // (destroyed first: waits for the thread)
+  ~RestartTask() { stop = true; }
+};
 
 // -------------------------------------------------------------------------
 // the method
@@ -2293,20 +2308,23 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
     proj_solve(s, ns, d, p, precond ? 1 : 0, w.H, ldh, tau_re_d, tau_im_d, w.G, w.Ascr,
                w.Zs, w.Cr, ldx, w.S, w.rho, w.singular);
     double t1 = host_now_ms();
-    // When the estimates already say that this cycle does not converge (the
-    // rule below, with the last cycle's norms, or ||B||, for ||Z~||), the
-    // restart's eigenproblem starts on a host thread now, beside the X
-    // update, the residuals and the next cycle's first product
-    std::future<RestartCoords> coords;
+    // When the estimates say that this cycle does not converge (the rule
+    // below, with the last cycle's norms, or ||B||, for ||Z~||), the restart's
+    // eigenproblem starts on a host thread now, beside the X update, the
+    // residuals and the next cycle's first product; should the cycle converge
+    // all the same (||Z~|| above ||B||), it is stopped
+    RestartTask restart;
     auto start_restart = [&]() {
-      coords = std::async(std::launch::async, restart_coordinates, bool(pl->symmetric), precond, d,
-                          p, k, ldh, keff, kp, std::ref(Hh));
+      HIPCHK(hipMemcpyAsync(Hh.data(), w.H, sizeof(double) * size_t(ldh) * ldh,
+                            hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      restart.coords = std::async(std::launch::async, restart_coordinates, bool(pl->symmetric),
+                                  precond, d, p, k, ldh, keff, kp, std::ref(Hh),
+                                  StopToken{&restart.stop});
     };
     HIPCHK(hipMemcpyAsync(rho.data(), w.rho, sizeof(double) * ns, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(Hh.data(), w.H, sizeof(double) * size_t(ldh) * ldh,
-                          hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
     if (cycle < pl->opts.max_cycles && !inf.inner_maxit_hit) {
+      HIPCHK(hipStreamSynchronize(s));
       bool finite = true, more = false;
       double rmax = 0.0;
       for (int q = 0; q < nt; ++q) {
@@ -2431,13 +2449,13 @@ expmv_status execute_impl(expmv_plan_s* pl, int transpose, const double* B, int 
     // from the eigensolve: it runs on the GPU while a host thread computes
     // the Ritz basis and the rotated H~.
     double t3 = host_now_ms();
-    if (!coords.valid()) start_restart();
+    if (!restart.coords.valid()) start_restart();
     const double ta = host_now_ms();
     apply_block(Vb + size_t(d / p) * blk);
     first_applied = true;
     const double tb = host_now_ms();
     ms_apply += tb - ta;
-    RestartCoords rcd = coords.get();
+    RestartCoords rcd = restart.coords.get();
     const int kn = rcd.kn;
     const int kpn = rcd.kpn;
     if (kn < 1 || kpn / p + 1 > m) {
