@@ -15,7 +15,7 @@
  *    CUDA tensor) unless the comment says "host".
  *  - Blocks (B, Z, G, X, Y) are n x p, row-major, contiguous: element (i, j)
  *    is at [i * p + j].  Values are FP64 at the boundary in every precision
- *    mode.
+ *    mode; a block may start at any FP64 element (16-byte alignment is faster).
  *  - CSR matrices use int32 row pointers (n + 1 entries, rowptr[0] = 0) and
  *    int32 column indices (nnz entries), FP64 values; column indices in a row
  *    need not be sorted.

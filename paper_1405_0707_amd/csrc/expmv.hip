@@ -656,6 +656,10 @@ void apply_K(expmv_plan_s* pl, int transpose, const T* X, T* Y, int p, double sc
   if (!staged && p == 2) return launch(k_spmm<T, 2, 1, kCgThreads>, 2, kCgThreads);
   if (p == 4 && pl->nnz > 16 * n) return launch(k_spmm<T, 4, 1, kCgThreads>, 4, kCgThreads);
   const int PP = pow2_lanes(p);
+  if (!aligned16(X, Y)) {   // a caller's blocks at an odd element
+    DISPATCH_PP(PP, launch(k_spmm<T, P_, 1, kCgThreads>, PP, kCgThreads));
+    return;
+  }
   DISPATCH_PP(PP, SPMM_DISPATCH(T, P_, p,
                                 launch(k_spmm<T, PPL_, VW_, kCgThreads>,
                                        p % 2 == 0 ? PP / 2 : PP, kCgThreads)));
@@ -3429,21 +3433,33 @@ expmv_status expmv_apply_operator(expmv_plan plan, int transpose, const double* 
   });
 }
 
+// Y = X value by value, between a caller's block that the inner solvers' vector
+// accesses cannot take (not 16-byte aligned) and the workspace
+static void copy_block(hipStream_t s, int64_t count, const double* X, double* Y) {
+  hipLaunchKernelGGL((k_convert<double, double>), dim3(512), dim3(kThreads), 0, s, count, X, Y, 1.0);
+}
+
 expmv_status expmv_apply_inverse(expmv_plan plan, int transpose, const double* X, int64_t p,
                                  void* work, size_t work_bytes, double* Y, long long* iters) {
   if (!plan || !X || !Y || p < 1 || p > kMaxP || p > plan->n) return EXPMV_EINVAL;
   return guarded([&]() -> expmv_status {
     bind_workspace(plan, int(p), 1, false, work, work_bytes);
     InnerResult r;
+    const int64_t cnt = plan->n * p;
     if (plan->mixed) {
       float* xf = reinterpret_cast<float*>(plan->ws.W);
       float* yf = reinterpret_cast<float*>(plan->ws.Wt);
-      const int64_t cnt = plan->n * p;
       hipLaunchKernelGGL((k_convert<double, float>), dim3(512), dim3(kThreads), 0, plan->stream,
                          cnt, X, xf, 1.0);
       r = apply_inverse<float>(plan, transpose, xf, yf, int(p));
       hipLaunchKernelGGL((k_convert<float, double>), dim3(512), dim3(kThreads), 0, plan->stream,
                          cnt, yf, Y, 1.0);
+    } else if (plan->kind == 0 && p % 2 == 0 && !small_solve(plan) && !aligned16(X, Y)) {
+      double* xa = reinterpret_cast<double*>(plan->ws.W);
+      double* ya = reinterpret_cast<double*>(plan->ws.Wt);
+      copy_block(plan->stream, cnt, X, xa);
+      r = apply_inverse<double>(plan, transpose, xa, ya, int(p));
+      copy_block(plan->stream, cnt, ya, Y);
     } else {
       r = apply_inverse<double>(plan, transpose, X, Y, int(p));
     }
@@ -3482,6 +3498,12 @@ expmv_status expmv_apply_preconditioner(expmv_plan plan, int transpose, const do
       apply(float(), xf, yf);
       hipLaunchKernelGGL((k_convert<float, double>), dim3(512), dim3(kThreads), 0, s, cnt, yf, Y,
                          1.0);
+    } else if (p % 2 == 0 && !aligned16(X, Y)) {
+      double* xa = reinterpret_cast<double*>(plan->ws.W);
+      double* ya = reinterpret_cast<double*>(plan->ws.Wt);
+      copy_block(s, cnt, X, xa);
+      apply(double(), xa, ya);
+      copy_block(s, cnt, ya, Y);
     } else {
       apply(double(), X, Y);
     }

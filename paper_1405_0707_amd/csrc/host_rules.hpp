@@ -2,6 +2,7 @@
 // that it can be checked on a CPU.
 #pragma once
 
+#include <cstdint>
 #include <mutex>
 #include <set>
 #include <utility>
@@ -19,6 +20,12 @@ namespace expmv {
 // ends within `most` of it.
 EXPMV_HOST_DEVICE inline int chunk_end(int b, int e, int most) {
   return e - b > most ? b + most : e;
+}
+
+// Whether kernels may read and write both blocks 16 bytes at a time.  Blocks of
+// the caller need only the alignment of their values.
+inline bool aligned16(const void* a, const void* b) {
+  return (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) % 16 == 0;
 }
 
 // Calls set() on the first use of `kernel` on `device` in the process, and

@@ -42,6 +42,10 @@ int main() {
   check(ordinary, "chunks of ordinary runs");
   check(at_the_limit, "chunks of runs that end near INT32_MAX");
 
+  alignas(16) static double block[8];
+  check(aligned16(block, block + 2) && !aligned16(block + 1, block) && !aligned16(block, block + 3),
+        "16-byte accesses only when both blocks are aligned");
+
   // several threads, each using every kernel on two devices: one set() per
   // kernel and device, finished before any thread goes on to its launch
   const int kernels = 6, threads = 8;
