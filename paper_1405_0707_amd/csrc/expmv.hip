@@ -1384,7 +1384,11 @@ void toeplitz_apply(expmv_plan_s* pl, const T* X, int64_t ldx, T* Y, int64_t ldy
   const double* dg = with_diag ? pl->tdiag.p : nullptr;
   const int q = (p + 1) / 2;
   const int64_t L = pl->L, n = pl->n;
-  if (const SmallRadices rad = small_radices(L, kSmallFftProduct); rad.passes && !accumulate) {
+  // (blocks that overlap in part take the streaming passes, which read all of X
+  // before they write Y; so do the inverses below)
+  if (const SmallRadices rad = small_radices(L, kSmallFftProduct);
+      rad.passes && !accumulate &&
+      same_or_apart(X, sizeof(T) * ((n - 1) * ldx + p), Y, sizeof(T) * ((n - 1) * ldy + p))) {
     launch_small_fft(pl, k_small_toeplitz<T>, rad, q, 1, int(n), p, X, ldx, Y, ldy, sym,
                      transpose ? dg : nullptr, transpose ? nullptr : dg, scale / double(L));
     return;
@@ -1431,7 +1435,9 @@ void toeplitz_gsf_n(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, do
   const cplx* g2 = tr ? pl->nsz.p : pl->ncz.p;
   // lengths that fit one workgroup's LDS: 43 us per call at n = 1,000, p = 2,
   // against 154 for the 32 launches below (n = 3,000, p = 16: 75 and 163)
-  if (const SmallRadices sr = small_radices(n, kSmallFftInverse); sr.passes) {
+  const size_t bytes = sizeof(T) * size_t(n) * p;
+  if (const SmallRadices sr = small_radices(n, kSmallFftInverse);
+      sr.passes && same_or_apart(V, bytes, W, bytes)) {
     launch_small_fft(pl, k_small_gsf_n<T>, sr, q, 2, p, V, W, f1, f2, g1, g2,
                      transpose ? nullptr : di, transpose ? di : nullptr, tr ? 0.0 : -1.0,
                      tr ? -1.0 : 0.0, scale / (2.0 * pl->x0));
@@ -1493,7 +1499,9 @@ void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, doub
   const int q = (p + 1) / 2;
   const int64_t L = pl->L, n = pl->n;
   // (52 us per call at n = 1,001, p = 2, against 110)
-  if (const SmallRadices rad = small_radices(L, kSmallFftInverse); rad.passes) {
+  const size_t bytes = sizeof(T) * size_t(n) * p;
+  if (const SmallRadices rad = small_radices(L, kSmallFftInverse);
+      rad.passes && same_or_apart(V, bytes, W, bytes)) {
     launch_small_fft(pl, k_small_gsf<T>, rad, q, 2, int(n), p, V, W, a1, a2, b1, b2,
                      transpose ? nullptr : di, transpose ? di : nullptr, scale / pl->x0);
     return;

@@ -2,6 +2,7 @@
 // that it can be checked on a CPU.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <mutex>
 #include <set>
@@ -26,6 +27,14 @@ EXPMV_HOST_DEVICE inline int chunk_end(int b, int e, int most) {
 // the caller need only the alignment of their values.
 inline bool aligned16(const void* a, const void* b) {
   return (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) % 16 == 0;
+}
+
+// Whether workgroups that each read some columns of one block and then write the
+// same columns of the other may run side by side: the blocks (bytes na, nb) are
+// apart or the same.
+inline bool same_or_apart(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return (x == y && na == nb) || x + na <= y || y + nb <= x;
 }
 
 // Calls set() on the first use of `kernel` on `device` in the process, and

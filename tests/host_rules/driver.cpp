@@ -46,6 +46,14 @@ int main() {
   check(aligned16(block, block + 2) && !aligned16(block + 1, block) && !aligned16(block, block + 3),
         "16-byte accesses only when both blocks are aligned");
 
+  const size_t d = sizeof(double);
+  check(same_or_apart(block, 4 * d, block, 4 * d) && same_or_apart(block, 4 * d, block + 4, 4 * d) &&
+            same_or_apart(block + 4, 4 * d, block, 4 * d) &&
+            !same_or_apart(block, 4 * d, block + 3, 4 * d) &&
+            !same_or_apart(block + 1, 4 * d, block, 4 * d) &&
+            !same_or_apart(block, 4 * d, block, 3 * d),
+        "columns in parallel only when the blocks are apart or the same");
+
   // several threads, each using every kernel on two devices: one set() per
   // kernel and device, finished before any thread goes on to its launch
   const int kernels = 6, threads = 8;
