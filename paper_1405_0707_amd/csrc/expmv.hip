@@ -1345,7 +1345,6 @@ void fft(expmv_plan_s* pl, const cplx* in, cplx* out, cplx* tmp, int q, double s
   fft_len(pl, pl->L, pl->radices, in, out, tmp, q, sign);
 }
 
-// the call's FFT work arrays must hold q complex columns
 // The passes of a length-L transform in one workgroup (small_fft.hpp); passes
 // = 0 when L is longer than `most` or has a prime factor above 5.
 SmallRadices small_radices(int64_t L, int most) {
@@ -1371,6 +1370,7 @@ void launch_small_fft(expmv_plan_s* pl, K kernel, const SmallRadices& rad, int q
   hipLaunchKernelGGL(kernel, dim3(q), dim3(kSmallFftThreads), lds, pl->stream, rad, args...);
 }
 
+// the call's FFT work arrays must hold q complex columns
 void check_fft_buffers(expmv_plan_s* pl, int q) {
   if (q > pl->ws.fq) throw StatusError{EXPMV_EINVAL};
 }
@@ -1731,14 +1731,22 @@ void shift_residuals(expmv_plan_s* pl, int transpose, const double* B, int p, co
 
 // Whether a block step of orthonormalize runs in one workgroup
 // (small_orth.hpp): up to four columns, a block in LDS, and a basis that one CU
-// reads (four times) and reduces (p^2 sums per panel) in less than the 53-60 us
-// of the 14 streaming launches.  A step takes 36 us there at n = 1,024, p = 4
-// (6 panels on average), 34 at n = 1,000, p = 2 (22 panels); at n = 4,096, p = 1
-// and 30 panels it lost (77 against 69 us with the product), and at n = 1,024,
-// p = 8 (509 against 433).
+// reads (four times) and reduces (p^2 sums per panel) faster than the 14
+// streaming launches, which take 65-120 us with the product at these sizes.  Basis
+// values npan n p from which one workgroup was slower (marginal time of a step of
+// a one-cycle Toeplitz solve, up to 62 panels):
+//   p = 1: n = 1,024 none, 3,000 75,000, 4,096 57,000, 6,144 55,000
+//   p = 2: n = 1,000 none, 1,536 100,000, 2,000 84,000, 3,000 108,000
+//   p = 3: n = 512 none, 1,000 110,000, 1,728 86,000, 2,000 90,000
+//   p = 4: n = 400 none, 1,024 82,000, 1,536 74,000
+// Larger blocks gain in the first 5 to 10 panels at most (n = 8,192, p = 1; 3,000,
+// p = 4 none); eight columns lost (n = 1,024: 509 against 433 us).  The bound on
+// npan n p^2 keeps p = 3 and 4 at 61,440 and 46,080 values, below their crossovers.
+// A single column stops at 57,344 values, below its crossovers from n = 3,000 on.
+// Kernel timing (opts.profile) is a matter of the streaming passes.
 bool small_orth(const expmv_plan_s* pl, int p, int npan) {
   const int64_t blk = pl->n * p;
-  return p <= kSmallOrthCols && blk <= kSmallOrthBlock && npan * blk <= 81920 &&
+  return p <= kSmallOrthCols && blk <= kSmallOrthBlock && npan * blk <= (p == 1 ? 57344 : 81920) &&
          npan * blk * p <= 184320 && pl->opts.profile <= 0;
 }
 
