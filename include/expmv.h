@@ -96,7 +96,12 @@ typedef struct {
   int preconditioned;  /* 1: Algorithm 2 (Krylov space of (tA)^{-1}), 0: Algorithm 1
                           (Krylov space of tA, no inner solve)                            */
   int profile;         /* 0: off; N > 0: time every N-th inner-solver iteration's
-                          kernels with HIP events (results in expmv_info.kern_*)          */
+                          kernels with HIP events (results in expmv_info.kern_*).  The
+                          timed kernels are the streaming ones: a small problem, whose
+                          inner solves and block steps otherwise run in one workgroup
+                          each, takes the streaming kernels while it is profiled (the
+                          same method and tolerances; other rounding, and times of
+                          kernels that it does not run with profile = 0)                 */
   int inner_refine;    /* mixed forms: rounds of FP64 iterative refinement of each FP32
                           inner solve (FP64 residual with the exact operator, FP32
                           correction solve); -1 = 1 for nonsymmetric A, 0 otherwise      */

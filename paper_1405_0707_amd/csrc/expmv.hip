@@ -1433,8 +1433,8 @@ void toeplitz_gsf_n(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, do
   // the second pair
   const cplx* g1 = tr ? pl->nsj.p : pl->ncx.p;
   const cplx* g2 = tr ? pl->nsz.p : pl->ncz.p;
-  // lengths that fit one workgroup's LDS: 43 us per call at n = 1,000, p = 2,
-  // against 154 for the 32 launches below (n = 3,000, p = 16: 75 and 163)
+  // lengths that fit one workgroup's LDS: 44 us per call at n = 1,000, p = 2,
+  // against 130 for the 32 launches below (n = 3,000, p = 16: 77 and 149)
   const size_t bytes = sizeof(T) * size_t(n) * p;
   if (const SmallRadices sr = small_radices(n, kSmallFftInverse);
       sr.passes && same_or_apart(V, bytes, W, bytes)) {
@@ -1498,7 +1498,7 @@ void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, doub
   const cplx* b2 = tr ? gzjx : gzy;
   const int q = (p + 1) / 2;
   const int64_t L = pl->L, n = pl->n;
-  // (52 us per call at n = 1,001, p = 2, against 110)
+  // (54 us per call at n = 1,009, p = 2, against 99)
   const size_t bytes = sizeof(T) * size_t(n) * p;
   if (const SmallRadices rad = small_radices(L, kSmallFftInverse);
       rad.passes && same_or_apart(V, bytes, W, bytes)) {

@@ -3,9 +3,9 @@
 // and pointwise step in LDS.
 //
 // The streaming passes of toeplitz.hpp cost one launch each, 2 to 3 us
-// whatever the length: at n = 1,000 an inverse took 32 launches and 154 us
-// for 16 KB of data (43 us here, 26 of them in the kernel; the source-term solve
-// 17.0 -> 11.9 ms).  Here a pass is a read of the column from LDS into
+// whatever the length: at n = 1,000 an inverse took 32 launches and 130-154 us
+// for 16 KB of data (44 us here, 26 of them in the kernel; the source-term solve
+// 17.5 -> 11.5 ms).  Here a pass is a read of the column from LDS into
 // registers, a barrier and a write back in place (Stockham order), with the
 // roots of unity in an LDS table made once per launch.  The bound is the
 // latency of the passes' barriers and of LDS.
@@ -31,7 +31,7 @@ constexpr int kSmallFftProduct = 2048, kSmallFftInverse = 3000;
 __device__ __host__ inline int small_fft_at(int i) { return i + (i >> 3); }
 
 // A transform length as radices 8, 4, 2, 5, 3 in pass order (at most 7 passes
-// up to 3,328, reached by 3^7 = 2,187)
+// up to 3,000, reached by 3^7 = 2,187)
 struct SmallRadices {
   int len, passes;
   unsigned char r[12];

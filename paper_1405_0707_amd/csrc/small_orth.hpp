@@ -6,8 +6,8 @@
 // again, update, then both Cholesky QR passes.  Bound: the latency of those
 // sweeps (one CU's L2 bandwidth would allow 2.7 us each at n = 1,728, 30 columns)
 // and of the p^2 wavefront sums per panel.  A step takes 34-37 us instead of
-// 53-60 and its launches' gaps: the source-term solve at n = 1,000 11.5 -> 9.4 ms,
-// 32^2, p = 4 4.4 -> 4.1, 12^3 upwind, p = 3 11.2 -> 10.3.
+// 53-60 and its launches' gaps: the source-term solve at n = 1,000 11.5 -> 8.3 ms,
+// 32^2, p = 4 4.3 -> 3.9, 12^3 upwind, p = 3 11.2 -> 10.1.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -5,8 +5,8 @@
 // The streaming kernels of kernels.hpp cost three (CG) or five (BiCGStab)
 // launches per iteration, 3 to 5 us each plus the gap before it, whatever the
 // size: at n = 1,024, p = 4 a CG iteration took 16 us for 0.16 MB of operands,
-// and takes 1.2 us here (the whole e^{tA}B 32 -> 4.5 ms; the 7-point upwind
-// operator at n = 1,728, p = 3: 37 -> 3.2 us, 60 -> 11 ms).
+// and takes 1.2 us here (the whole e^{tA}B 31.9 -> 4.3 ms; the 7-point
+// upwind operator at n = 1,728, p = 3: 37 -> 3.2 us, 60.2 -> 11.2 ms).
 // Here the operator's rows (values and 16-bit column indices) stay in
 // registers for the whole solve, the vectors in registers and LDS, and an
 // iteration costs three (five) workgroup barriers and one LDS gather per
