@@ -724,14 +724,17 @@ int grid_lanes(int64_t n, int lanes, int nt) {
 // of two), two columns per lane when p is even: the rows in one pass.  Every
 // workgroup of an update sums the partials of all of them (16 PP bytes each), so
 // g workgroups read 16 PP g^2 bytes from the caches.  With one column per lane
-// the rows take twice the workgroups; above 20 MB they take two passes instead:
-// n = 8,000, p = 31 read 260 MB, u3 / u1 / u2 took 32 / 31 / 18 us, the inverse
-// 6.6 ms, now 3.1; 181^2, p = 5 (33 MB) 16.1 ms, now 12.3.  255^2, p = 3 (17 MB) is
-// faster in one pass (a time sweep 41.1 against 42.5 ms).
+// the rows take twice the workgroups; above 8 MB they take two passes instead (the
+// updates one, with 1024 threads): n = 8,000, p = 31 read 260 MB, u3 / u1 / u2 took
+// 32 / 31 / 18 us, the inverse 6.6 ms, now 3.1; 181^2, p = 5 (33 MB) 16.1, now 12.3; 255^2,
+// p = 3 (17 MB) a time sweep 42.5, now 41.3; upwind 26^3, p = 5 (10 MB) gains 8%.  Where
+// 512 workgroups need two passes anyway, 33 MB cost less than fewer workgroups
+// (40^3 upwind, p = 5 3.8 against 4.0 ms).
 int cg_grid(int64_t n, int PP, int p) {
   if (p % 2 == 0) return grid_lanes(n, PP / 2, kCgThreads);
   const int g = grid_lanes(n, PP, kCgThreads);
-  return p == 1 || 16.0 * PP * g * g <= 20e6 ? g : grid_lanes(n, PP, 2 * kCgThreads);
+  const double most = n * PP <= kCgGrid * kCgThreads ? 8e6 : 40e6;
+  return p == 1 || 16.0 * PP * g * g <= most ? g : grid_lanes(n, PP, 2 * kCgThreads);
 }
 
 // Workgroup size of the vector updates.  Odd p, one column per lane: 1024
@@ -740,10 +743,14 @@ int cg_grid(int64_t n, int PP, int p) {
 // of the larger workgroups cost more.  Jacobi-CG with 512 and 1024 threads:
 // 300^2 p = 5 (3 passes) 19.3 and 22.6 ms, p = 9 (6) 35.0 and 38.3, p = 17 (11)
 // 62.5 and 58.9; 500^2 p = 5 (8) 56.9 and 59.4, p = 9 (16) 98.3 and 96.7, p = 17
-// (31) 182 and 164, p = 3 (4) 32.1 and 31.0; p = 1 no gain.
+// (31) 182 and 164, p = 3 (4) 32.1 and 31.0; p = 1 no gain.  Also where cg_grid halves
+// a grid that 512 threads would have covered in one pass, which 1024 still do
+// (181^2, p = 5 7.9 and 7.3 ms).
 int cg_update_threads(int64_t n, int PP, int p) {
   if (p % 2 == 0 || p == 1) return kCgThreads;
-  return n * PP > (int64_t(PP <= 4 ? 4 : 10) << 18) ? 1024 : kCgThreads;
+  const int64_t lanes = n * PP;
+  const bool halved = lanes <= kCgGrid * kCgThreads && cg_grid(n, PP, p) * kCgThreads < lanes;
+  return halved || lanes > (int64_t(PP <= 4 ? 4 : 10) << 18) ? 1024 : kCgThreads;
 }
 
 double inner_tol_of(expmv_plan_s* pl) {
