@@ -437,8 +437,8 @@ __device__ __forceinline__ void lds_barrier() {
 // and the gather waits for LDS instead of memory.  Same sums in the same
 // order.  Every thread of the workgroup runs the same chunks.
 // Bound: memory; the 128^3 product at p = 16 (7 nonzeros per row) takes 243 us in
-// the BiCGStab (1.34 GB counted, 5.5 TB/s) against 290 us for
-// csr_rows_pipelined, and 202 us alone (569 us with one column per lane and no
+// the BiCGStab (1.44 GB counted, 5.9 TB/s; 0.99 without the neighbour rows that are
+// fetched again) against 290 us (1.25 GB) for csr_rows_pipelined, and 202 us alone (569 us with one column per lane and no
 // staging); in FP32 at 1024^2, p = 32, 147 against 232 us.
 template <int S, int U, int PPL, int VW, int NT, typename T, typename Body>
 __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,

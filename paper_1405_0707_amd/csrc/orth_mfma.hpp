@@ -371,19 +371,22 @@ k_panel_gemm_mma(int64_t n, int p_arg, const T* __restrict__ V, int npan,
   }
 }
 
-// The update passes (kUpdProj, kUpdGram) of an FP64 basis with p <= 16 columns
-// per panel.  k_orth_mma splits the rows over its wavefronts for the update and
-// the basis columns for the projection, so that it reads V twice (counted: 1.97
-// times V at 17 panels; the second time from the 256 MB cache) and C once per 16
-// rows.  Here eight wavefronts take 16 rows per step and own the column blocks
+// The update passes (kUpdProj, kUpdGram) of an FP64 basis with 8 or 16 columns
+// per panel (a block of 16 basis columns is two panels or one, and a lane's four
+// columns one 32-byte run; other widths and FP32 bases keep k_orth_mma, not
+// measured here).  k_orth_mma splits the rows over its wavefronts for the update
+// and the basis columns for the projection, so that its projecting update reads V
+// twice (counted over the 128^3 solve: 11.0 GB at 5.5 GB of V, here 5.5) and C once
+// per 16 rows.  Here eight wavefronts take 16 rows per step and own the column blocks
 // wave, wave + 8, ... throughout: their part of C and their projection sums stay
 // in registers, and a block of V is loaded once, in both operand layouts (the
 // second after the first is used, from the cache).  Per step the wavefronts' parts of V C meet
 // in LDS (two buffers, one barrier) and each forms W' for itself.  Same products
 // in FP64; the sum over basis columns is grouped by wavefront.  Bound: memory.
 // At n = 2^20, p = 16 (2.4 GB at 16 panels): projecting update 865 -> 612 us and
-// Gram update 663 -> 471 at 16 panels, 963 -> 880 and 721 -> 531 at 17; with p = 8
-// at 64^3 the pass sum goes from 3.8 to 3.5 ms per solve.
+// Gram update 663 -> 471 at 16 panels, 963 -> 880 and 721 -> 531 at 17; at 2^21, 20.5
+// panels on average, 2,262 -> 1,929 (3.1 TB/s) and 1,696 -> 1,228 (4.9); with p = 8 at 64^3
+// the pass sum goes from 3.8 to 3.5 ms per solve.
 // MB = column blocks per wavefront (npan p <= 128 MB); PC = p = 16 or 8 (a
 // column block is one panel or two).  The projecting update takes 146 and 178
 // registers at MB = 3 and 4, hence one workgroup per CU (at two it spills: 972 us
