@@ -628,7 +628,7 @@ void toeplitz_gsf(expmv_plan_s* pl, int transpose, const T* V, T* W, int p, doub
 int grid_lanes(int64_t n, int lanes, int nt);
 
 // Whether the SpMMs stage the operator's entries through LDS (spmm_rows).
-int staged_rows(const expmv_plan_s* pl) { return pl->nnz <= 8 * pl->n ? 1 : 0; }
+int staged_rows(const expmv_plan_s* pl) { return stage_entries(pl->nnz, pl->n) ? 1 : 0; }
 
 // Y = scale K X (K = -tA, or its transpose) for n x p blocks of type T.
 //

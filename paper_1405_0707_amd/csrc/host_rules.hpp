@@ -16,11 +16,20 @@
 
 namespace expmv {
 
-// End of the chunk of at most `most` entries that starts at b in the run
-// [b, e), 0 <= b <= e.  By difference: b + most passes INT32_MAX where a run
-// ends within `most` of it.
+// Longest staged chunk of CSR entries (csr_rows_staged), and whether an
+// operator's entries are staged: rows of at most 8 on average (longer ones would
+// leave most lanes idle in each chunk), and entries that end a chunk short of
+// INT32_MAX, as chunk_end and the fetch one chunk ahead add up to that to 32-bit
+// indices (forming them by difference cost the 128^3 product 0.6%).
+constexpr int kStageMost = 2048;
+inline bool stage_entries(int64_t nnz, int64_t n) {
+  return nnz <= 8 * n && nnz <= INT32_MAX - kStageMost;
+}
+
+// End of the chunk of at most `most` (<= kStageMost) entries that starts at b in
+// the run [b, e), 0 <= b <= e <= INT32_MAX - kStageMost.
 EXPMV_HOST_DEVICE inline int chunk_end(int b, int e, int most) {
-  return e - b > most ? b + most : e;
+  return b + most < e ? b + most : e;
 }
 
 // Whether kernels may read and write both blocks 16 bytes at a time.  Blocks of

@@ -448,6 +448,7 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
                                        int64_t seg0, int64_t seg1, int32_t* sj, double* sv,
                                        Body&& body) {
   constexpr int TR = NT / PPL, CH = NT * S;
+  static_assert(CH <= kStageMost, "entries per chunk (stage_entries)");
   if (seg0 >= seg1) return;
   const int tid = threadIdx.x;
   int64_t r0 = seg0, row = seg0 + tid / PPL;
@@ -458,9 +459,9 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
   auto fetch = [&](int b, int e) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const int i = tid + s * NT;
-      js[s] = i < e - b ? colind[b + i] : 0;
-      vs[s] = i < e - b ? val[b + i] : 0.0;
+      const int i = b + tid + s * NT;
+      js[s] = i < e ? colind[i] : 0;
+      vs[s] = i < e ? val[i] : 0.0;
     }
   };
   auto extents = [&](int64_t r, int& a, int& b) {
@@ -482,7 +483,7 @@ __device__ inline void csr_rows_staged(const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int i = tid + s * NT;
-      if (i < ce - cb) {
+      if (cb + i < ce) {
         sj[buf + i] = js[s];
         sv[buf + i] = vs[s];
       }
@@ -549,8 +550,7 @@ constexpr int spmm_stage() {
 }
 
 // The rows of this workgroup's segment (NT threads) of y = K x or K D^{-1} x:
-// body(row, sums).  staged: rows of at most 8 nonzeros on average (longer
-// rows would leave most lanes idle in each chunk).
+// body(row, sums).  staged: stage_entries.
 template <typename T, int PPL, int VW, int NT, typename Body>
 __device__ inline void spmm_rows(int staged, int64_t n, const int32_t* __restrict__ rowptr,
                                  const int32_t* __restrict__ colind,

@@ -15,7 +15,7 @@ namespace expmv {
 
 // V = DFT_R(v): V_m = sum_r v_r exp(sign 2 pi i r m / R), in few operations (the
 // radix-512 pass at L = 2^20, 8 columns: 128 registers instead of 190, two
-// workgroups per CU instead of one, 79 -> 53 us; the full sums of R products
+// workgroups per CU instead of one, 79 -> 58.5 us; the full sums of R products
 // cost 64 complex multiplications at R = 8, these two)
 template <int R>
 __device__ inline void dft_small(const cplx (&v)[R], cplx (&V)[R], double sign) {

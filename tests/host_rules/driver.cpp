@@ -26,6 +26,8 @@ static bool covers(int b, int e, int most) {
   for (int steps = 0; at < e; ++steps) {
     const int ce = chunk_end(int(at), e, most);
     if (ce <= at || ce > e || ce - at > most || steps > 100) return false;
+    volatile int fetched = ce + most;   // the fetch one chunk ahead
+    if (fetched < ce) return false;
     at = ce;
   }
   return at == e && chunk_end(e, e, most) == e;
@@ -36,9 +38,14 @@ int main() {
   for (int most : {512, 1024, 2048})
     for (int len : {0, 1, 511, 512, 513, 2047, 2048, 2049, 10000}) {
       ordinary = ordinary && covers(0, len, most) && covers(12345, 12345 + len, most);
-      for (int gap : {0, 1, 7, 511, 2048})
+      // up to the last operator that is staged
+      for (int gap : {kStageMost, kStageMost + 1, kStageMost + 7})
         at_the_limit = at_the_limit && covers(INT_MAX - gap - len, INT_MAX - gap, most);
     }
+  const int64_t n = int64_t(1) << 30;
+  check(stage_entries(INT_MAX - kStageMost, n) && !stage_entries(INT_MAX - kStageMost + 1, n) &&
+            stage_entries(80, 10) && !stage_entries(81, 10),
+        "which operators are staged");
   check(ordinary, "chunks of ordinary runs");
   check(at_the_limit, "chunks of runs that end near INT32_MAX");
 
